@@ -441,6 +441,9 @@ twed_status noalloc_scratch(void **out)
 
 // ---- batch ----------------------------------------------------------------------
 
+constexpr int kBatchTickets = 4;
+constexpr int kSplitItems = 64;  // symmetric items per resident wave from which the width classes run apart
+
 struct BatchLayout {
     void *rowsX, *rowsY, *offX, *offY, *order, *zero, *bnd, *flags, *tmpD;
     size_t total;
@@ -459,7 +462,7 @@ BatchLayout batch_layout(char *base, int64_t totX, int64_t nX, int64_t maxX, int
     L.offX = c.take((size_t)(nX + 1) * 8);
     L.offY = symmetric ? L.offX : c.take((size_t)(nY + 1) * 8);
     L.order = c.take((size_t)nX * 4);
-    L.zero = c.take(8);  // batch tickets: one per launch of the sweep
+    L.zero = c.take(kBatchTickets * 4);  // batch tickets: one per launch of the sweep
     // single-pair sweep state for pairs too long for one wave
     const int64_t maxlen = std::max(maxX, maxY);
     const int64_t kshort = twed_batch_max_short_length(prm->dim);
@@ -630,7 +633,7 @@ twed_status batch_enqueue(const BatchPlan &P, const void *X, const void *TX, con
     twed_status s = TWED_OK;
     hipError_t e;
     e = launch_stage(prec, cp, X, TX, (const int64_t *)L.offX, nX, 0, maxX, totX + nX, L.rowsX,
-                     (uint32_t *)L.zero, 2, st);
+                     (uint32_t *)L.zero, kBatchTickets, st);
     if (e != hipSuccess) return fail_hip(e, "staging launch");
     // one short query reads the caller's collection as it is (no staging
     // pass); every other sweep reads staged rows
@@ -659,29 +662,31 @@ twed_status batch_enqueue(const BatchPlan &P, const void *X, const void *TX, con
     b.ticket = (uint32_t *)L.zero;
     if (b.nItems > 0xffffffffLL) return fail(TWED_ERR_UNSUPPORTED, "more than 2^32 - 1 pairs in one call");
     // Width classes: a pair's K (columns per lane) is ceil(shorter length /
-    // 64).  Only pairs of K <= 8 need no more than the narrow kernel; in the
-    // symmetric case the longest-first order puts every pair of K > 8 (both
-    // series longer than 512 samples) before the others, so the items split
-    // into a wide launch and a narrow one.
+    // 64).  The longest-first order of the symmetric case puts the pairs of a
+    // larger K before all others, so its items split into one launch per
+    // class, each with the registers (and so the waves per SIMD) of its own
+    // widths.  The widths over 8, whose kernel fits only one or two waves, are
+    // always split off; the others where a launch has kSplitItems items per
+    // resident wave, since each launch ends with waves that wait for its last
+    // tickets (1-D FP32, 2,048 series of 64 .. 1,024: 105.5 ms in two launches,
+    // 98.6 ms in three; 1-D FP64, 500 series of 100 .. 500, 40 items per wave:
+    // 3.71 ms in one, 3.95 ms in two).
     const int kmax = batch_kmax(cp.dimt);
-    const int64_t k_need = (std::min(maxX, maxY) + kWaveLanes - 1) / kWaveLanes;
-    int64_t split = 0;  // symmetric: items [0, split) hold the pairs of K > 8
-    int kclass = kBatchAll;
-    if (k_need <= kBatchNarrowMax || kmax <= kBatchNarrowMax) {
-        kclass = kBatchNarrow;
-    } else if (sym) {
-        int64_t J = 0;  // first series (in the order) of at most 512 samples
-        while (J < nX && offX[P.order[J] + 1] - offX[P.order[J]] > (int64_t)kBatchNarrowMax * kWaveLanes) ++J;
-        split = J * (J - 1) / 2;
-        kclass = -1;  // two launches
-    }
+    const int64_t k_need = std::min<int64_t>((std::min(maxX, maxY) + kWaveLanes - 1) / kWaveLanes, kmax);
+    const int kclass = batch_class_for(k_need);
+    // Rectangular chains share a series of X, or one of Y where only those fit
+    // the lanes of the kernel or where Y is the smaller collection (longer
+    // chains).
+    const int64_t kclass_max = kclass == kBatchSlim ? kBatchSlimMax : (kclass == kBatchNarrow ? kBatchNarrowMax : kmax);
+    const int64_t kfit = kWaveLanes * std::min<int64_t>(kclass_max, kmax);
+    b.y_fixed = maxX > kfit ? maxY <= kfit : (maxY <= kfit && nY < nX && nY < kWaveLanes);
     const int cus = std::max(1, device_simds() / 4);
     auto workers_of = [&](int cls) {
         int wk = batch_max_workers(prec, cp, cls);
         if (P.cfg.waves_per_cu > 0) wk = std::min(wk, P.cfg.waves_per_cu * cus);
         return wk;
     };
-    int workers = workers_of(kclass < 0 ? kBatchNarrow : kclass);
+    const int workers = workers_of(kclass);
     if (workers <= 0) return fail(TWED_ERR_DEVICE, "occupancy query failed");
     if (sym) {
         e = launch_batch_diag_zero(prec, Dk, nX, st);
@@ -693,43 +698,43 @@ twed_status batch_enqueue(const BatchPlan &P, const void *X, const void *TX, con
                               (uint32_t *)L.zero, (int)std::min<int64_t>((nY + 63) / 64, workers), st);
         if (e != hipSuccess) return fail_hip(e, "batch launch");
     } else if (b.nItems > 0) {
-        int64_t chunk = P.cfg.chunk;
-        if (chunk <= 0) {
-            // items per ticket: about 64k cells of work per ticket for short
-            // pairs, while leaving at least four tickets per wave
-            const double cells = (double)totX / (double)nX * (double)totY / (double)nY;
-            chunk = std::max<int64_t>(1, std::min<int64_t>(32, (int64_t)(65536.0 / std::max(cells, 1.0))));
-            chunk = std::min<int64_t>(chunk, std::max<int64_t>(1, b.nItems / (4 * (int64_t)workers)));
-        }
-        b.chunk = (int)chunk;
-        if (kclass >= 0) {
-            b.kclass = kclass;
-            b.grid = (int)std::min<int64_t>((b.nItems + chunk - 1) / chunk, workers);
-            e = launch_batch(prec, cp, b, st);
-            if (e != hipSuccess) return fail_hip(e, "batch launch");
-        } else {
-            // the wide pairs first (longest first), then the narrow ones on
-            // the second ticket
+        // first item whose shorter series has at most 64*k samples (symmetric)
+        auto items_over = [&](int k) {
+            int64_t J = 0;
+            while (J < nX && offX[P.order[J] + 1] - offX[P.order[J]] > (int64_t)k * kWaveLanes) ++J;
+            return J * (J - 1) / 2;
+        };
+        int64_t item = sym ? items_over(kmax) : 0;  // (those before go to the single-pair sweep)
+        // Ends item range [item, end) with the launch of one class.
+        auto launch_part = [&](int n, int cls, int64_t end) -> twed_status {
+            if (end <= item) return TWED_OK;
             BatchArgs w = b;
-            w.kclass = kBatchWide;
-            w.nItems = split;
-            const int wide_workers = workers_of(kBatchWide);
-            if (wide_workers <= 0) return fail(TWED_ERR_DEVICE, "occupancy query failed");
-            w.grid = (int)std::min<int64_t>((split + chunk - 1) / chunk, wide_workers);
-            if (split > 0) {
-                e = launch_batch(prec, cp, w, st);
-                if (e != hipSuccess) return fail_hip(e, "batch launch");
-            }
-            BatchArgs nrw = b;
-            nrw.kclass = kBatchNarrow;
-            nrw.item0 = split;
-            nrw.ticket = (uint32_t *)L.zero + 1;
-            nrw.grid = (int)std::min<int64_t>((b.nItems - split + chunk - 1) / chunk, workers);
-            if (b.nItems > split) {
-                e = launch_batch(prec, cp, nrw, st);
-                if (e != hipSuccess) return fail_hip(e, "batch launch");
-            }
+            w.item0 = item;
+            w.nItems = end;
+            w.ticket = (uint32_t *)L.zero + n;
+            w.kclass = cls;
+            const int wk = workers_of(w.kclass);
+            if (wk <= 0) return fail(TWED_ERR_DEVICE, "occupancy query failed");
+            w.chunk = P.cfg.chunk > 0 ? P.cfg.chunk
+                                      : batch_default_chunk(prec, cp.dimt, (double)totX / (double)nX,
+                                                            (double)totY / (double)nY, b.y_fixed != 0,
+                                                            w.nItems - item, wk);
+            const int64_t tickets = (w.nItems - item + w.chunk - 1) / w.chunk;
+            w.grid = (int)std::min<int64_t>(tickets, wk);
+            item = end;
+            e = launch_batch(prec, cp, w, st);
+            return e != hipSuccess ? fail_hip(e, "batch launch") : TWED_OK;
+        };
+        int rest = kclass;
+        if (sym && kclass == kBatchAll) {
+            if ((s = launch_part(0, kBatchWide, items_over(kBatchNarrowMax))) != TWED_OK) return s;
+            rest = kBatchNarrow;
         }
+        if (sym && rest == kBatchNarrow && b.nItems - item >= (int64_t)kSplitItems * workers_of(kBatchNarrow)) {
+            if ((s = launch_part(1, kBatchMid, items_over(kBatchSlimMax))) != TWED_OK) return s;
+            rest = kBatchSlim;
+        }
+        if ((s = launch_part(2, rest, b.nItems)) != TWED_OK) return s;
     }
 
     // listed pairs whose shorter series exceeds one wave (the batch kernel

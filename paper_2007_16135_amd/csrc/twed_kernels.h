@@ -184,20 +184,31 @@ struct BatchArgs {
     int chunk;                   // consecutive items per ticket (0 or 1: one)
     int64_t item0;               // first item of this launch (items item0 .. nItems-1)
     int kclass;                  // kernel of the pair widths swept (BatchClass)
+    int y_fixed;                 // rectangular: items run Y-major (item = b*nX + a), chains share Y_b
 };
 // Pair widths (columns per lane K) a batch kernel sweeps; pairs outside its
-// range are left to another launch.  One kernel for every width holds the
-// registers of the widest, which limits it to two waves per SIMD; narrower
-// kernels fit more.
+// range are left to another launch.  A kernel holds the registers of its
+// widest pairs, so the narrower kernels fit more waves per SIMD (1-D FP32:
+// eight, five, four and two for the widths up to 2, 4, 8 and 16).
 enum BatchClass : int {
     kBatchAll = 0,     // K = 1 .. KMAX
     kBatchNarrow = 1,  // K = 1 .. min(8, KMAX)
-    kBatchWide = 2     // K = 9 .. KMAX (one-component samples only)
+    kBatchWide = 2,    // K = 9 .. KMAX (one-component samples only)
+    kBatchMid = 3,     // K = 5 .. 8 (KMAX >= 8)
+    kBatchSlim = 4     // K = 1 .. min(4, KMAX)
 };
+constexpr int kBatchSlimMax = 4;
 constexpr int kBatchNarrowMax = 8;
+// The kernel for a launch that meets pairs of up to k_need columns per lane.
+inline int batch_class_for(int64_t k_need)
+{
+    return k_need <= kBatchSlimMax ? kBatchSlim : (k_need <= kBatchNarrowMax ? kBatchNarrow : kBatchAll);
+}
 constexpr int kWaveLanes = 64;  // lanes of a wave (gfx950 runs wave64)
 hipError_t launch_batch(Prec prec, const CostParams &cp, const BatchArgs &a, hipStream_t st);
 int batch_kmax(int dimt);
+// Items per ticket for pairs of series of these mean lengths.
+int batch_default_chunk(Prec prec, int dimt, double mean_x, double mean_y, bool y_fixed, int64_t items, int workers);
 // One query of at most kLaneMaxQuery samples (staged rows rowsQ) against nY
 // series: one lane per pair, D[j] = TWED(query, Y_j); ticket zeroed.  The
 // series are the staged rows rowsY, or, with Yraw non-null, the caller's

@@ -411,3 +411,59 @@ def test_batch_plan_tune_bitwise(tmp_path):
     for p in (plan, plan2, plan3, qplan):
         p.close()
     tw.twed_tune_clear()
+
+
+@pytest.mark.parametrize("dim,p,prec", [(1, 1.0, "f32"), (1, 1.0, "f64"), (3, 2.0, "f64"), (2, 3.0, "f32_acc64"),
+                                        (8, 2.0, "f32")])
+def test_chained_pairs_bitwise(dim, p, prec):
+    # Enough short pairs that a wave sweeps several in one chain: lengths at
+    # the edges of the 64-row chunks and of the columns per lane.  The
+    # symmetric matrix is checked against the oracle; the rectangular forms
+    # (chains along X and along Y) and pair lists (runs of one X, runs of one
+    # Y, shuffled, entries outside the collections in between) give the same
+    # bits.
+    rng = np.random.default_rng(67)
+    edge = [1, 2, 62, 63, 64, 65, 66, 126, 127, 128, 129, 190, 193, 255, 256]
+    n = 420
+    lens = [edge[k % len(edge)] if k % 3 else int(rng.integers(1, 100)) for k in range(n)]
+    col = synth.pack([synth.walk(rng, L, dim) for L in lens], [synth.irregular_times(rng, L) for L in lens])
+    X, T = to_dev(col, prec)
+    kw = dict(nu=0.01, lam=0.5, p=p, precision=prec)
+    say(f"chained symmetric dim{dim} p{p} {prec}")
+    D = tw.twed_batch(X, T, col.off, **kw)
+    Dm = D.cpu().numpy()
+    assert np.array_equal(Dm, Dm.T) and np.all(np.diag(Dm) == 0)
+    prs = rng.integers(0, n, (1500, 2))
+    prs = prs[prs[:, 0] != prs[:, 1]]
+    Xr, Tr = ref_inputs(col, prec)
+    ref = oracle.get().pairs(Xr, Tr, col.off, Xr, Tr, col.off, prs, 0.01, 0.5, p)
+    assert max_rel(Dm[prs[:, 0], prs[:, 1]], ref) <= TOL[prec]
+
+    off_diag = ~np.eye(n, dtype=bool)
+    say("chained rectangular, along Y and along X")
+    R = tw.twed_batch(X, T, col.off, X, T, col.off, **kw).cpu().numpy()
+    assert np.array_equal(R[off_diag], Dm[off_diag])
+    few = col.subset(range(5, 11))
+    F, TF = to_dev(few, prec)
+    many = col.subset(np.tile(np.arange(n), 20))
+    M, TM = to_dev(many, prec)
+    want = np.tile(Dm, (20, 1))[:, 5:11]
+    same = np.tile(np.arange(n), 20)[:, None] == np.arange(5, 11)[None]
+    R = tw.twed_batch(M, TM, many.off, F, TF, few.off, **kw).cpu().numpy()
+    assert np.array_equal(R[~same], want[~same])
+    R = tw.twed_batch(F, TF, few.off, M, TM, many.off, **kw).cpu().numpy().T
+    assert np.array_equal(R[~same], want[~same])
+
+    a, b = np.nonzero(off_diag)
+    for name, order in (("runs of X", np.arange(len(a))), ("runs of Y", np.lexsort((a, b))),
+                        ("shuffled", rng.permutation(len(a)))):
+        say(f"chained pair list, {name}")
+        pl = np.stack([a[order], b[order]], 1).astype(np.int64)
+        bad = rng.choice(len(pl), 400, replace=False)
+        pl[bad[:200], 0] = n
+        pl[bad[200:], 1] = -1
+        got = tw.twed_batch(X, T, col.off, X, T, col.off, pairs=torch.as_tensor(pl, device="cuda"), **kw).cpu().numpy()
+        ok = np.ones(len(pl), dtype=bool)
+        ok[bad] = False
+        assert np.all(np.isnan(got[bad]))
+        assert np.array_equal(got[ok], Dm[pl[ok, 0], pl[ok, 1]])
