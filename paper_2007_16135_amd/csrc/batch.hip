@@ -516,118 +516,6 @@ __global__ __launch_bounds__(64, (chain_waves<CT, AT, DIMT, KHI>())) void batch_
     }
 }
 
-// One short query against many series: one lane per pair.  The query (at
-// most kLaneMaxQuery samples) sits in LDS and every lane reads the same row
-// at the same time (a broadcast); each lane sweeps its own series column by
-// column with the query's DP column in registers.  Every cell is evaluated
-// with the arithmetic of lane_row (transposed, which changes nothing: the
-// point and time terms are symmetric and the minimum is exact), so results
-// are bitwise those of the wave-per-pair sweep and of twed_pair.  It
-// replaces that sweep for this shape because a wave per pair would spend
-// most of its lanes and steps filling and draining a 64-lane pipeline for a
-// few hundred cells.
-//
-// RAW: the series are read as the caller holds them (Y: dim components per
-// sample, TY: timestamps) instead of as staged rows, and each sample's
-// deletion cost is computed from the sample before it with the staging
-// kernel's arithmetic, so a collection queried once needs no staging pass
-// (a staged collection, reused by many queries, reads its rows instead).
-template <typename CT, typename AT, int DIMT, int PM, bool RAW>
-__global__ __launch_bounds__(kWave) void batch_lane_kernel(const CT *__restrict__ rowsQ, int nQ,
-                                                           const CT *__restrict__ rowsY,
-                                                           const CT *__restrict__ Yraw,
-                                                           const CT *__restrict__ TYraw, int dim,
-                                                           const int64_t *__restrict__ offY, int64_t nY,
-                                                           CostArgs<CT> ca, AT *D, uint32_t *ticket)
-{
-    constexpr int S = Row<CT, DIMT>::kStride;
-    constexpr int QM = kLaneMaxQuery;
-    __shared__ CT q[(QM + 1) * S];
-    const int lane = threadIdx.x;
-    for (int k = lane; k < (nQ + 1) * S; k += kWave) q[k] = rowsQ[k];
-    __syncthreads();
-    const AT INF = pinf<AT>();
-    for (;;) {
-        const int64_t first = (int64_t)next_ticket(ticket) * kWave;
-        if (first >= nY) break;
-        const int64_t item = first + lane;
-        const bool ok = item < nY;
-        const int64_t b = ok ? item : first;  // idle lanes repeat a pair and store nothing
-        const int64_t yb = offY[b];
-        const int lb = (int)(offY[b + 1] - yb);
-        const CT *rb = rowsY + (yb + b) * S;
-        int maxL = lb;
-#pragma unroll
-        for (int m = kWave / 2; m >= 1; m >>= 1) {
-            const int o = __shfl_xor(maxL, m, kWave);
-            maxL = o > maxL ? o : maxL;
-        }
-        // DP(i, j-1) and X(i, j-1) of the query rows i = 0..nQ
-        AT up[QM + 1], xq[QM + 1];
-        up[0] = AT(0);
-        xq[0] = AT(0);
-#pragma unroll
-        for (int i = 1; i <= QM; ++i) {
-            up[i] = INF;
-            xq[i] = INF;
-        }
-        AT res = INF;
-        CT px[DIMT], pt = CT(0);  // RAW: the sample before (the zero pad at j = 1)
-#pragma unroll
-        for (int k = 0; k < DIMT; ++k) px[k] = CT(0);
-        for (int j = 1; j <= maxL; ++j) {
-            Row<CT, DIMT> bj;
-            if constexpr (RAW) {
-                // columns past lb repeat sample lb (nothing reads them)
-                const int64_t r = yb + (j <= lb ? j : lb) - 1;
-#pragma unroll
-                for (int k = 0; k < DIMT; ++k) bj.x[k] = k < dim ? Yraw[r * dim + k] : CT(0);
-                bj.t = TYraw[r];
-                const CT d = point_dist<DIMT, PM, CT>(bj.x, px, ca.p, ca.invp);
-                bj.del = fma_(ca.nu, fabs_(bj.t - pt), d) + ca.lambda;
-#pragma unroll
-                for (int k = 0; k < DIMT; ++k) px[k] = bj.x[k];
-                pt = bj.t;
-            } else {
-                load_row<CT, DIMT>(rb, j <= lb ? j : lb, bj);
-            }
-            const AT bdel = (AT)bj.del;
-            AT above = INF;       // DP(i-1, j), starting at the pad row
-            AT diag = xq[0];      // X(i-1, j-1)
-            // an offset the compiler cannot see through: the query rows are
-            // read from LDS in every column instead of being hoisted out of
-            // the column loop (all of them would not fit in registers)
-            uint32_t qo = 0;
-            asm volatile("" : "+v"(qo));
-#pragma unroll
-            for (int i = 1; i <= QM; ++i) {
-                if (i <= nQ) {
-                    Row<CT, DIMT> a;
-#pragma unroll
-                    for (int k = 0; k < DIMT; ++k) a.x[k] = q[qo + i * S + k];
-                    a.t = q[qo + i * S + DIMT];
-                    a.del = q[qo + i * S + DIMT + 1];
-                    const CT dist = point_dist<DIMT, PM, CT>(a.x, bj.x, ca.p, ca.invp);
-                    const AT e = (AT)fma_(ca.nu, fabs_(a.t - bj.t), dist);
-                    const AT v = dmin(dmin(diag + e, above + (AT)a.del), up[i] + bdel);
-                    diag = xq[i];
-                    xq[i] = v + e;
-                    up[i] = v;
-                    above = v;
-                }
-            }
-            up[0] = INF;
-            xq[0] = INF;
-            AT last = up[1];
-#pragma unroll
-            for (int i = 2; i <= QM; ++i)
-                if (i == nQ) last = up[i];
-            res = j == lb ? last : res;
-        }
-        if (ok) D[item] = res;
-    }
-}
-
 // Calls f<KLO, KHI>() with the widths of a class, as far as the sample width
 // allows them (a class that reaches beyond KMAX stops there).
 template <typename CT, typename AT, int DIMT, int PM, typename F>
@@ -700,24 +588,6 @@ hipError_t launch_batch(Prec prec, const CostParams &cp, const BatchArgs &a, hip
                                    a.chunk > 1 ? a.chunk : 1);
             return hipGetLastError();
         });
-    });
-}
-
-hipError_t launch_batch_lane(Prec prec, const CostParams &cp, const void *rowsQ, int nQ, const void *rowsY,
-                            const void *Yraw, const void *TYraw, const int64_t *offY, int64_t nY, void *D,
-                            uint32_t *ticket, int grid, hipStream_t st)
-{
-    if (nQ < 1 || nQ > kLaneMaxQuery) return hipErrorInvalidValue;
-    return by_prec(prec, cp.dimt, cp.pm, [&]<typename CT, typename AT, int DIMT, int PM>() -> hipError_t {
-        if (Yraw)
-            hipLaunchKernelGGL((batch_lane_kernel<CT, AT, DIMT, PM, true>), dim3(grid), dim3(kWave), 0, st,
-                               (const CT *)rowsQ, nQ, nullptr, (const CT *)Yraw, (const CT *)TYraw, cp.dim, offY,
-                               nY, CostArgs<CT>::make(cp), (AT *)D, ticket);
-        else
-            hipLaunchKernelGGL((batch_lane_kernel<CT, AT, DIMT, PM, false>), dim3(grid), dim3(kWave), 0, st,
-                               (const CT *)rowsQ, nQ, (const CT *)rowsY, nullptr, nullptr, cp.dim, offY, nY,
-                               CostArgs<CT>::make(cp), (AT *)D, ticket);
-        return hipGetLastError();
     });
 }
 

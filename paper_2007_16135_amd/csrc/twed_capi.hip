@@ -694,8 +694,7 @@ twed_status batch_enqueue(const BatchPlan &P, const void *X, const void *TX, con
     }
     if (b.nItems > 0 && lane) {
         // one short query: a lane per pair
-        e = launch_batch_lane(prec, cp, L.rowsX, (int)maxX, L.rowsY, Y, TY, (const int64_t *)L.offY, nY, Dk,
-                              (uint32_t *)L.zero, (int)std::min<int64_t>((nY + 63) / 64, workers), st);
+        e = launch_batch_lane(prec, cp, L.rowsX, (int)maxX, L.rowsY, Y, TY, (const int64_t *)L.offY, nY, Dk, st);
         if (e != hipSuccess) return fail_hip(e, "batch launch");
     } else if (b.nItems > 0) {
         // first item whose shorter series has at most 64*k samples (symmetric)

@@ -467,3 +467,34 @@ def test_chained_pairs_bitwise(dim, p, prec):
         ok[bad] = False
         assert np.all(np.isnan(got[bad]))
         assert np.array_equal(got[ok], Dm[pl[ok, 0], pl[ok, 1]])
+
+
+@pytest.mark.parametrize("prec", ["f64", "f32", "f32_acc64"])
+def test_short_query_row_split_bitwise(prec):
+    # A short query's rows are split over the waves of a workgroup: query
+    # lengths at the edges of the split (fewer rows than waves, uneven rows,
+    # both register sizes), sample widths whose 16-byte units end inside a
+    # sample, a collection that starts off a 16-byte boundary, and the same
+    # collection staged once.  Every entry equals the pair-list sweep's bits.
+    rng = np.random.default_rng(71)
+    dt = torch.float64 if prec == "f64" else torch.float32
+    f = lambda a: torch.as_tensor(np.ascontiguousarray(a), dtype=dt, device="cuda")
+    for nq, dim, p, shift in ((1, 4, 2.0, 1), (3, 3, 2.0, 0), (4, 1, 1.0, 1), (15, 9, 1.0, 0), (16, 17, 2.0, 0),
+                              (17, 5, 3.0, 0), (28, 6, 2.0, 1), (29, 20, 2.0, 0), (31, 31, 2.0, 0), (32, 32, 1.0, 0)):
+        lens = np.concatenate([[1, 2, 1], rng.integers(1, 70, 190)])
+        off = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+        Y = f(np.concatenate([np.zeros(shift), rng.standard_normal((off[-1], dim)).cumsum(0).ravel()]))[shift:]
+        Y = Y.view(int(off[-1]), dim)
+        TY = f(np.cumsum(rng.exponential(1.0, off[-1])))
+        q, tq = f(rng.standard_normal((nq, dim)).cumsum(0)), f(np.cumsum(rng.exponential(1.0, nq)))
+        offq = np.array([0, nq], dtype=np.int64)
+        kw = dict(nu=0.05, lam=0.7, p=p, precision=prec)
+        say(f"query split {prec} nq {nq} dim {dim}")
+        prs = torch.as_tensor(np.stack([np.zeros(len(lens)), np.arange(len(lens))], 1).astype(np.int64), device="cuda")
+        want = tw.twed_batch(q, tq, offq, Y.clone(), TY, off, pairs=prs, **kw).cpu().numpy()
+        got = tw.twed_batch(q, tq, offq, Y, TY, off, **kw).cpu().numpy().reshape(-1)
+        assert np.array_equal(got, want), (nq, dim)
+        plan = tw.BatchPlan(offq, off, dim=dim, nu=0.05, lam=0.7, p=p, precision=prec)
+        plan.stage_y(Y, TY)
+        assert np.array_equal(plan.run(q, tq).cpu().numpy().reshape(-1), want), (nq, dim, "staged")
+        plan.close()
