@@ -535,6 +535,240 @@ bool conv_staged_enabled()
     return !(env && std::strcmp(env, "generic") == 0);
 }
 
+// ---- the whole forward pass of a window of rows ----------------------------------
+//
+// Layer by layer, every 64-channel activation goes through HBM: 256 bytes per row
+// and layer, which bounds the two inner layers at 2.9 TB/s (20,000 series of 128
+// .. 512 samples: 1.47 ms, of which 35 MB of inputs and embeddings need 7 us).
+// Here a workgroup carries a window of 384 rows through all four layers in LDS:
+// features in (8 bytes per row), layer-4 outputs out (16).  A window's edge rows
+// lack neighbours, two more of them per layer, so 372 of its rows are stored and
+// windows overlap by 12.  The weights of all layers (90 KB) stay in LDS, one
+// workgroup of eight waves fills a compute unit, and each wave computes 48 rows by
+// all 64 columns: 7 fragment reads per 12 matrix instructions, so that LDS reads
+// (448 cycles per step of 32 channels) and matrix cores (384) are about level.
+// The fragments, their order and the roundings between layers are those of
+// conv_kernel, so the embeddings are the same bits.
+constexpr int kFwWaves = 8;
+constexpr int kFwBlocks = 3;                             // 16-row blocks per wave
+constexpr int kFwRows = kFwWaves * kFwBlocks * 16;       // rows of a window
+constexpr int kFwHalo = 2 * (kLayers - 1);               // rows at each end that layer 4 cannot use
+constexpr int kFwOut = kFwRows - 2 * kFwHalo;
+constexpr int kFwHs = 80;                                // staged row of 64 channels
+constexpr int kFwWs = 336;                               // staged row of a 64-channel layer's weights
+constexpr int kFwW1s = 40;                               // .. of layer 1's (10 inputs, zeros to 32)
+
+struct FwArgs {
+    const uint16_t *feat;
+    const uint32_t *row_info;
+    const uint16_t *wt[kLayers];  // [C_out][5 C_in]
+    const float *bias[kLayers];
+    float *y4;
+    int64_t R;
+};
+
+__global__ __launch_bounds__(64 * kFwWaves, 2) void forward_kernel(FwArgs g, int nWindows)
+{
+    __shared__ __align__(16) uint16_t hS[(kFwRows + 4) * kFwHs];  // window row r at index r + 2
+    __shared__ __align__(16) uint16_t w1S[64 * kFwW1s];
+    __shared__ __align__(16) uint16_t wS[2][64 * kFwWs];
+    __shared__ __align__(16) uint16_t w4S[kC4 * kFwWs];
+    __shared__ uint32_t featS[kFwRows + 4];                          // window row r at index r + 2
+    constexpr int kThreads = 64 * kFwWaves;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int li = lane & 15, kq = lane >> 4;
+
+    for (int idx = tid; idx < 64 * (kFwW1s / 2); idx += kThreads) {
+        const int n = idx / (kFwW1s / 2), d = idx - n * (kFwW1s / 2);
+        const uint32_t v = d < kKsize ? *reinterpret_cast<const uint32_t *>(g.wt[0] + n * 2 * kKsize + 2 * d) : 0u;
+        *reinterpret_cast<uint32_t *>(w1S + w_slot(n) * kFwW1s + 2 * d) = v;
+    }
+    for (int idx = tid; idx < 2 * 64 * 40; idx += kThreads) {
+        const int l = idx / (64 * 40), u = idx - l * 64 * 40, n = u / 40;
+        *reinterpret_cast<uint4 *>(wS[l] + w_slot(n) * kFwWs + (u - n * 40) * 8) =
+            *reinterpret_cast<const uint4 *>(g.wt[1 + l] + (int64_t)u * 8);
+    }
+    for (int idx = tid; idx < kC4 * 40; idx += kThreads) {
+        const int n = idx / 40;
+        *reinterpret_cast<uint4 *>(w4S + n * kFwWs + (idx - n * 40) * 8) =
+            *reinterpret_cast<const uint4 *>(g.wt[3] + (int64_t)idx * 8);
+    }
+
+    // features and row words of a window: registers, then LDS
+    uint32_t fv = 0u, info[kFwBlocks];
+    auto load_window = [&](int64_t g0) {
+        const int64_t gr = g0 - 2 + tid;
+        fv = tid < kFwRows + 4 && gr >= 0 && gr < g.R ? *reinterpret_cast<const uint32_t *>(g.feat + 2 * gr) : 0u;
+#pragma unroll
+        for (int i = 0; i < kFwBlocks; ++i) {
+            const int64_t m = g0 + (w * kFwBlocks + i) * 16 + li;
+            info[i] = m >= 0 && m < g.R ? g.row_info[m] : 0u;  // L = 0: no tap valid
+        }
+    };
+    const int row0 = w * kFwBlocks * 16 + li;  // this lane's row of block 0
+    uint32_t valid[kFwBlocks];
+    f32x4 acc[kFwBlocks][4];
+    // acc += W' h^T over 320 inputs; NB column blocks of the weights at ws
+    // (MASKED: some row of the wave lacks a neighbour in its own series)
+    auto inner = [&]<int NB, bool MASKED>(const uint16_t *ws) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < kFwBlocks; ++i)
+#pragma unroll
+            for (int j = 0; j < NB; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int ks = 0; ks < 2 * kKsize; ++ks) {
+            const int tap = ks / 2, half = ks % 2;
+            bf16x8 hf[kFwBlocks], wf[NB];
+#pragma unroll
+            for (int i = 0; i < kFwBlocks; ++i) {
+                const uint4 v = lds4(hS + (row0 + 16 * i + tap) * kFwHs + 32 * half + 8 * kq);
+                const bool ok = !MASKED || ((valid[i] >> tap) & 1u);
+                hf[i] = frag8(ok ? v.x : 0u, ok ? v.y : 0u, ok ? v.z : 0u, ok ? v.w : 0u);
+            }
+#pragma unroll
+            for (int j = 0; j < NB; ++j) {
+                // (layer 4 has four columns: the rest of its block repeats them)
+                const uint4 v = lds4(ws + (NB == 1 ? li & 3 : 16 * j + li) * kFwWs + 32 * ks + 8 * kq);
+                wf[j] = frag8(v.x, v.y, v.z, v.w);
+            }
+#pragma unroll
+            for (int i = 0; i < kFwBlocks; ++i)
+#pragma unroll
+                for (int j = 0; j < NB; ++j) acc[i][j] = mfma32(wf[j], hf[i], acc[i][j]);
+        }
+    };
+    // bias, ReLU, bf16: the layer's outputs take the place of its inputs
+    auto store_h = [&](const float (&bias)[16]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < kFwBlocks; ++i) {
+#pragma unroll
+            for (int h2 = 0; h2 < 2; ++h2) {
+                const int n0 = 32 * h2 + 8 * kq;
+                uint32_t o[4];
+#pragma unroll
+                for (int pr = 0; pr < 4; ++pr) {
+                    const f32x4 &A = acc[i][2 * h2 + pr / 2];
+                    const int e = 2 * (pr % 2);
+                    float v0 = A[e] + bias[8 * h2 + 2 * pr], v1 = A[e + 1] + bias[8 * h2 + 2 * pr + 1];
+                    v0 = v0 > 0.f ? v0 : 0.f;
+                    v1 = v1 > 0.f ? v1 : 0.f;
+                    o[pr] = (uint32_t)__builtin_bit_cast(uint16_t, (__bf16)v0) |
+                            ((uint32_t)__builtin_bit_cast(uint16_t, (__bf16)v1) << 16);
+                }
+                *reinterpret_cast<uint4 *>(hS + (row0 + 16 * i + 2) * kFwHs + n0) = uint4{o[0], o[1], o[2], o[3]};
+            }
+        }
+    };
+
+    float bias[kLayers - 1][16];  // of this lane's columns 8 kq .. + 7 and 32 + 8 kq .. + 7
+#pragma unroll
+    for (int l = 0; l < kLayers - 1; ++l)
+#pragma unroll
+        for (int c = 0; c < 16; ++c) bias[l][c] = g.bias[l][32 * (c / 8) + 8 * kq + c % 8];
+    float bias4[kC4];
+#pragma unroll
+    for (int c = 0; c < kC4; ++c) bias4[c] = g.bias[kLayers - 1][c];
+
+    // rows -2, -1 and kFwRows, + 1 of the window only feed rows that are not stored
+    for (int idx = tid; idx < 4 * kFwHs; idx += kThreads) {
+        const int r = idx / kFwHs;
+        hS[(r < 2 ? r : kFwRows + r) * kFwHs + idx % kFwHs] = 0;
+    }
+    if ((int)blockIdx.x < nWindows) load_window((int64_t)blockIdx.x * kFwOut - kFwHalo);
+    for (int win = blockIdx.x; win < nWindows; win += gridDim.x) {
+        const int64_t g0 = (int64_t)win * kFwOut - kFwHalo;
+        if (tid < kFwRows + 4) featS[tid] = fv;
+#pragma unroll
+        for (int i = 0; i < kFwBlocks; ++i) {
+            const int t = row_t(info[i]), L = row_L(info[i]);
+            uint32_t bits = 0;
+#pragma unroll
+            for (int tap = 0; tap < kKsize; ++tap) {
+                const int ts = t + tap - kKsize / 2;
+                if (ts >= 0 && ts < L) bits |= 1u << tap;
+            }
+            valid[i] = bits;
+        }
+        __syncthreads();
+        if (win + (int)gridDim.x < nWindows) load_window((int64_t)(win + gridDim.x) * kFwOut - kFwHalo);
+        // layer 1: one step of 32 inputs, k = 8 kq + e: taps 4 kq .. 4 kq + 3, two channels each
+        {
+            bf16x8 hf[kFwBlocks], wf[4];
+#pragma unroll
+            for (int i = 0; i < kFwBlocks; ++i) {
+                uint32_t d[4] = {0u, 0u, 0u, 0u};
+#pragma unroll
+                for (int hh = 0; hh < 4; ++hh) {
+                    const int tap = 4 * kq + hh;
+                    if (tap < kKsize && ((valid[i] >> tap) & 1u)) d[hh] = featS[row0 + 16 * i + tap];
+                }
+                hf[i] = frag8(d[0], d[1], d[2], d[3]);
+            }
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const uint4 v = lds4(w1S + (16 * j + li) * kFwW1s + 8 * kq);
+                wf[j] = frag8(v.x, v.y, v.z, v.w);
+            }
+#pragma unroll
+            for (int i = 0; i < kFwBlocks; ++i)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) acc[i][j] = mfma32(wf[j], hf[i], f32x4{0.f, 0.f, 0.f, 0.f});
+        }
+        bool masked = false;
+#pragma unroll
+        for (int i = 0; i < kFwBlocks; ++i) masked = masked || valid[i] != (1u << kKsize) - 1u;
+        const bool any_masked = __ballot(masked) != 0;  // uniform
+        auto layer = [&]<int NB>(const uint16_t *ws) __attribute__((always_inline)) {
+            if (any_masked) inner.template operator()<NB, true>(ws);
+            else inner.template operator()<NB, false>(ws);
+        };
+        store_h(bias[0]);  // (the last window's layer 4 was read before the barrier above)
+        __syncthreads();
+        layer.template operator()<4>(wS[0]);
+        __syncthreads();
+        store_h(bias[1]);
+        __syncthreads();
+        layer.template operator()<4>(wS[1]);
+        __syncthreads();
+        store_h(bias[2]);
+        __syncthreads();
+        layer.template operator()<1>(w4S);
+        if (kq == 0) {
+#pragma unroll
+            for (int i = 0; i < kFwBlocks; ++i) {
+                const int r = row0 + 16 * i;
+                const int64_t m = g0 + r;
+                if (r >= kFwHalo && r < kFwRows - kFwHalo && m < g.R) {
+                    const f32x4 &A = acc[i][0];
+                    *reinterpret_cast<float4 *>(g.y4 + m * 4) =
+                        float4{A[0] + bias4[0], A[1] + bias4[1], A[2] + bias4[2], A[3] + bias4[3]};
+                }
+            }
+        }
+    }
+}
+
+hipError_t launch_forward(const uint16_t *feat, const uint32_t *row_info, const uint16_t *const *wt,
+                          const float *const *bias, float *y4, int64_t R, hipStream_t st)
+{
+    if (R <= 0) return hipSuccess;
+    FwArgs g{};
+    g.feat = feat;
+    g.row_info = row_info;
+    for (int l = 0; l < kLayers; ++l) {
+        g.wt[l] = wt[l];
+        g.bias[l] = bias[l];
+    }
+    g.y4 = y4;
+    g.R = R;
+    const int64_t windows = (R + kFwOut - 1) / kFwOut;
+    if (windows > 0x7fffffffLL) return hipErrorInvalidValue;
+    const int grid = (int)std::min<int64_t>(windows, std::max(1, device_cus()));
+    hipLaunchKernelGGL(forward_kernel, dim3(grid), dim3(64 * kFwWaves), 0, st, g, (int)windows);
+    return hipGetLastError();
+}
+
 // ---- weight gradient ------------------------------------------------------------------
 //
 // dW[u][c][n] = sum_r [row r reads its own series at tap u] h[r + u - 2][c] dy[r][n].

@@ -73,6 +73,12 @@ hipError_t launch_gemm(int out_mode, const GemmArgs &g, int splitk, hipStream_t 
 // weight gradient takes the per-wave tile kernel (a cross-check of the staged ones).
 bool conv_staged_enabled();
 
+// All four layers over R packed rows without their activations: features (2
+// channels) in, y4 [R][4] f32 out; wt and bias per layer (wt 16-byte aligned).
+// The same bits as the layers one by one.
+hipError_t launch_forward(const uint16_t *feat, const uint32_t *row_info, const uint16_t *const *wt,
+                          const float *const *bias, float *y4, int64_t R, hipStream_t st);
+
 // Weight and bias gradient of one convolution layer in one pass, written (not
 // added) to gWb[0 .. 5 cin cout + cout): dW (kKsize, cin, cout) then db (cout).
 // h [R][cin] and dy [R][cout] bf16 packed rows, row words as in GemmArgs.

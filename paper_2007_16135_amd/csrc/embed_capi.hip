@@ -116,6 +116,14 @@ hipError_t forward(const float *params, const Weights &w, const Acts &a, const f
 {
     hipError_t e = launch_features(X, off, nS, row_base, R, maxlen, a.row_info, a.row_series, a.feat, st);
     if (e != hipSuccess) return e;
+    if (!a.row_series && conv_staged_enabled()) {
+        // no activation is kept: all layers in one launch
+        const float *bias[kLayers];
+        for (int l = 0; l < kLayers; ++l) bias[l] = params + layer_offset(l) + layer_w_count(l);
+        e = launch_forward(a.feat, a.row_info, w.wt, bias, a.y4, R, st);
+        if (e != hipSuccess) return e;
+        return launch_pool(a.y4, off, nS, row_base, R, emb, emb16, sqnorm, st);
+    }
     const uint16_t *in = a.feat;
     for (int l = 0; l < kLayers; ++l) {
         void *out = l < kLayers - 1 ? (void *)a.h[l] : (void *)a.y4;

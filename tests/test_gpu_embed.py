@@ -455,3 +455,21 @@ def test_knn_long_series_exhaustive():
     for q in range(len(lens_q)):
         np.testing.assert_allclose(dist[q], np.sort(D[q])[:4], rtol=1e-5)
         np.testing.assert_allclose(D[q, ids[q]], dist[q], rtol=1e-5)
+
+
+@pytest.mark.parametrize("lens", [[1], [371], [372], [373], [744, 1], [370, 2, 3, 369], [1, 2, 3, 4, 5] * 160,
+                                  [1500], [17] * 400, [372] * 60])
+def test_forward_windows_match_layers_bitwise(lens, generic_gemm):
+    # The one-launch forward pass stores 372 rows per window: collections that
+    # end at, before and behind a window's edge, series across several windows,
+    # series shorter than the kernel width, more windows than compute units.
+    # The embeddings are the bits of the layers swept one by one.
+    rng = np.random.default_rng(sum(lens))
+    off = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    X = dev(np.cumsum(rng.standard_normal(off[-1])))
+    vec = dev(knn.init_params(7) + 0.05 * rng.standard_normal(B.twed_embed_param_count()).astype(np.float32))
+    say(f"embed windows: {len(lens)} series, {off[-1]} rows")
+    got = B.twed_embed_forward(vec, X, off).cpu().numpy()
+    with generic_gemm:
+        want = B.twed_embed_forward(vec, X, off).cpu().numpy()
+    assert np.isfinite(got).all() and np.array_equal(got, want)
