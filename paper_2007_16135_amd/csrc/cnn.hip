@@ -976,18 +976,28 @@ __global__ __launch_bounds__(256) void conv_wgrad_kernel(const uint16_t *__restr
     }
 }
 
-// out[e] = sum_g partial[g][e], g in order, e < row_len (a multiple of 4).
-// Block: 16 float4 columns x 16 slices of g; slice sums combine in order.
-__global__ __launch_bounds__(256) void partial_sum_kernel(const float *__restrict__ partial, int G, int row_len,
-                                                          float *__restrict__ out)
+// out[l][e] = sum_g partial[l][g][e], g in order, e < row_len[l] (a multiple of
+// 4), for every layer l in one launch (blockIdx.y; one per layer took 4 .. 6 us
+// each).  Block: 16 float4 columns x 16 slices of g; slice sums combine in order.
+struct PartialArgs {
+    const float *partial[kLayers];
+    float *out[kLayers];
+    int row_len[kLayers];
+    int G;
+};
+
+__global__ __launch_bounds__(256) void partial_sum_kernel(PartialArgs g)
 {
     __shared__ float4 red[16][16];
+    const int row_len = g.row_len[blockIdx.y];
+    const float *__restrict__ partial = g.partial[blockIdx.y];
+    float *__restrict__ out = g.out[blockIdx.y];
     const int col = threadIdx.x & 15, sl = threadIdx.x >> 4;
     const int e4 = (blockIdx.x * 16 + col) * 4;
     float4 s = float4{0.f, 0.f, 0.f, 0.f};
     if (e4 < row_len) {
 #pragma unroll 4
-        for (int gi = sl; gi < G; gi += 16) {
+        for (int gi = sl; gi < g.G; gi += 16) {
             const float4 v = *reinterpret_cast<const float4 *>(partial + (int64_t)gi * row_len + e4);
             s.x += v.x;
             s.y += v.y;
@@ -1022,9 +1032,9 @@ static int wgrad_groups(int64_t R)
 
 static int wgrad_row_len(int cin, int cout) { return kKsize * cin * cout + cout; }
 
-size_t conv_wgrad_partial_bytes(int64_t R)
+size_t conv_wgrad_partial_bytes(int cin, int cout, int64_t R)
 {
-    return (size_t)wgrad_groups(R) * (size_t)wgrad_row_len(64, 64) * sizeof(float);
+    return (size_t)wgrad_groups(R) * (size_t)wgrad_row_len(cin, cout) * sizeof(float);
 }
 
 bool conv_wgrad_fits(int cin, int cout)
@@ -1033,7 +1043,7 @@ bool conv_wgrad_fits(int cin, int cout)
 }
 
 hipError_t launch_conv_wgrad(int cin, int cout, const uint16_t *h, const uint32_t *row_info, const uint16_t *dy,
-                             int64_t R, float *partial, float *gWb, hipStream_t st)
+                             int64_t R, float *partial, hipStream_t st)
 {
     if (!conv_wgrad_fits(cin, cout) || R > 0x7fffffffLL) return hipErrorInvalidValue;
     if (((uintptr_t)h | (uintptr_t)dy) & 7u || (uintptr_t)partial & 15u) return hipErrorInvalidValue;
@@ -1050,10 +1060,22 @@ hipError_t launch_conv_wgrad(int cin, int cout, const uint16_t *h, const uint32_
     else
         hipLaunchKernelGGL((conv_wgrad_kernel<2, 64>), dim3(G), dim3(256), 0, st, h, row_info, dy, (int)R, chunks,
                            partial, row_len);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(partial_sum_kernel, dim3((row_len / 4 + 15) / 16), dim3(256), 0, st, partial, G, row_len,
-                       gWb);
+    return hipGetLastError();
+}
+
+hipError_t launch_wgrad_sums(const float *const *partial, float *const *gWb, int64_t R, hipStream_t st)
+{
+    PartialArgs g{};
+    g.G = wgrad_groups(R);
+    if (g.G == 0) return hipSuccess;
+    int longest = 0;
+    for (int l = 0; l < kLayers; ++l) {
+        g.partial[l] = partial[l];
+        g.out[l] = gWb[l];
+        g.row_len[l] = wgrad_row_len(kChan[l], kChan[l + 1]);
+        longest = std::max(longest, g.row_len[l]);
+    }
+    hipLaunchKernelGGL(partial_sum_kernel, dim3((longest / 4 + 15) / 16, kLayers), dim3(256), 0, st, g);
     return hipGetLastError();
 }
 
@@ -1181,15 +1203,22 @@ __global__ __launch_bounds__(256) void colsum_kernel(const uint16_t *__restrict_
     }
 }
 
-// Mean pair loss (log(1+p) - log(1+d))^2 with p = sqrt(|e_a - e_b|^2 + eps):
-// one wave per pair, two embedding components per lane.
-__global__ __launch_bounds__(64) void pair_loss_kernel(const float *__restrict__ emb, const int32_t *__restrict__ pairs,
-                                                       const float *__restrict__ target, int P, int nSeries,
-                                                       float inv_P, float *__restrict__ demb,
-                                                       float *__restrict__ loss_sum)
+// Mean pair loss (log(1+p) - log(1+d))^2 with p = sqrt(|e_a - e_b|^2 + eps): a
+// wave per pair, two embedding components per lane.  A wave takes every
+// (4 gridDim)-th pair and a workgroup adds its share of the loss once: an
+// addition per pair to the one loss word took 20 of the 29 us of 2,048 pairs.
+constexpr int kLossWaves = 4;
+__global__ __launch_bounds__(64 * kLossWaves) void pair_loss_kernel(const float *__restrict__ emb,
+                                                                   const int32_t *__restrict__ pairs,
+                                                                   const float *__restrict__ target, int P,
+                                                                   int nSeries, float inv_P, float *__restrict__ demb,
+                                                                   float *__restrict__ loss_sum)
 {
-    const int lane = threadIdx.x;
-    for (int p = blockIdx.x; p < P; p += gridDim.x) {
+    __shared__ float part[kLossWaves];
+    const int lane = threadIdx.x & 63;
+    const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    float loss = 0.f;
+    for (int64_t p = (int64_t)blockIdx.x * kLossWaves + w; p < P; p += (int64_t)gridDim.x * kLossWaves) {
         const int64_t ia = pairs[2 * p], ib = pairs[2 * p + 1];
         if (ia < 0 || ia >= nSeries || ib < 0 || ib >= nSeries) continue;  // uniform: one pair per wave
         const float d0 = emb[ia * kEmb + lane] - emb[ib * kEmb + lane];
@@ -1204,7 +1233,15 @@ __global__ __launch_bounds__(64) void pair_loss_kernel(const float *__restrict__
         atomicAdd(demb + ia * kEmb + 64 + lane, coef * d1);
         atomicAdd(demb + ib * kEmb + lane, -coef * d0);
         atomicAdd(demb + ib * kEmb + 64 + lane, -coef * d1);
-        if (lane == 0) atomicAdd(loss_sum, r * r * inv_P);
+        loss += r * r * inv_P;
+    }
+    if (lane == 0) part[w] = loss;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        float sum = 0.f;
+#pragma unroll
+        for (int k = 0; k < kLossWaves; ++k) sum += part[k];
+        atomicAdd(loss_sum, sum);
     }
 }
 
@@ -1224,18 +1261,35 @@ __global__ void adamw_kernel(float *__restrict__ w, float *__restrict__ m, float
     }
 }
 
-__global__ void weight_copies_kernel(const float *__restrict__ w, int cin, int cout, uint16_t *__restrict__ wt,
-                                     uint16_t *__restrict__ wb)
+// The bf16 operand copies of every layer's weights, and zeros in up to two
+// arrays of floats (training: the embedding gradient and the loss), in one
+// launch instead of seven of 3 .. 4 us each.
+struct PrepareArgs {
+    const float *w[kLayers];
+    uint16_t *wt[kLayers], *wb[kLayers];
+    float *zero[2];
+    int64_t zero_n[2];
+};
+
+__global__ void prepare_kernel(PrepareArgs g)
 {
-    const int total = kKsize * cin * cout;
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < total; i += gridDim.x * blockDim.x) {
-        // i = (tap*cin + c)*cout + n
-        const int n = i % cout, k = i / cout;
-        const int tap = k / cin, c = k - (k / cin) * cin;
-        const uint16_t h = to_bf16(w[i]);
-        wt[(int64_t)n * (kKsize * cin) + k] = h;
-        wb[(int64_t)c * (kKsize * cout) + (kKsize - 1 - tap) * cout + n] = h;
+    const int64_t id = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, n_threads = (int64_t)gridDim.x * blockDim.x;
+#pragma unroll
+    for (int l = 0; l < kLayers; ++l) {
+        constexpr int kC[kLayers + 1] = {kChan[0], kChan[1], kChan[2], kChan[3], kChan[4]};
+        const int cin = kC[l], cout = kC[l + 1];
+        for (int64_t i = id; i < kKsize * cin * cout; i += n_threads) {
+            // i = (tap*cin + c)*cout + n
+            const int n = (int)i % cout, k = (int)i / cout;
+            const int tap = k / cin, c = k - (k / cin) * cin;
+            const uint16_t h = to_bf16(g.w[l][i]);
+            g.wt[l][(int64_t)n * (kKsize * cin) + k] = h;
+            g.wb[l][(int64_t)c * (kKsize * cout) + (kKsize - 1 - tap) * cout + n] = h;
+        }
     }
+#pragma unroll
+    for (int z = 0; z < 2; ++z)
+        for (int64_t i = id; i < g.zero_n[z]; i += n_threads) g.zero[z][i] = 0.f;
 }
 
 __global__ void fill_kernel(float *__restrict__ p, int64_t n, float v)
@@ -1290,8 +1344,9 @@ hipError_t launch_pair_loss(const float *emb, const int32_t *pairs, const float 
                             float *demb, float *loss_sum, hipStream_t st)
 {
     if (P <= 0) return hipSuccess;
-    const int grid = P < 16384 ? P : 16384;
-    hipLaunchKernelGGL(pair_loss_kernel, dim3(grid), dim3(64), 0, st, emb, pairs, target, P, nSeries,
+    // four pairs per wave, and at most 4,096 workgroups
+    const int grid = std::min((P + 4 * kLossWaves - 1) / (4 * kLossWaves), 4096);
+    hipLaunchKernelGGL(pair_loss_kernel, dim3(grid), dim3(64 * kLossWaves), 0, st, emb, pairs, target, P, nSeries,
                        1.0f / (float)P, demb, loss_sum);
     return hipGetLastError();
 }
@@ -1306,10 +1361,20 @@ hipError_t launch_adamw(float *w, float *m, float *v, const float *g, int64_t n,
     return hipGetLastError();
 }
 
-hipError_t launch_weight_copies(const float *w, int cin, int cout, uint16_t *wt, uint16_t *wb, hipStream_t st)
+hipError_t launch_prepare(const float *const *w, uint16_t *const *wt, uint16_t *const *wb, float *zero0, int64_t n0,
+                          float *zero1, int64_t n1, hipStream_t st)
 {
-    hipLaunchKernelGGL(weight_copies_kernel, dim3(grid_for((int64_t)kKsize * cin * cout)), dim3(256), 0, st, w, cin,
-                       cout, wt, wb);
+    PrepareArgs g{};
+    for (int l = 0; l < kLayers; ++l) {
+        g.w[l] = w[l];
+        g.wt[l] = wt[l];
+        g.wb[l] = wb[l];
+    }
+    g.zero[0] = zero0;
+    g.zero_n[0] = n0;
+    g.zero[1] = zero1;
+    g.zero_n[1] = n1;
+    hipLaunchKernelGGL(prepare_kernel, dim3(grid_for(std::max<int64_t>(kParamCount, n0), 256, 1024)), dim3(256), 0, st, g);
     return hipGetLastError();
 }
 

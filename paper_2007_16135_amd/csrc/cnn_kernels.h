@@ -79,15 +79,17 @@ bool conv_staged_enabled();
 hipError_t launch_forward(const uint16_t *feat, const uint32_t *row_info, const uint16_t *const *wt,
                           const float *const *bias, float *y4, int64_t R, hipStream_t st);
 
-// Weight and bias gradient of one convolution layer in one pass, written (not
-// added) to gWb[0 .. 5 cin cout + cout): dW (kKsize, cin, cout) then db (cout).
+// Weight and bias gradient of one convolution layer in one pass: per-workgroup
+// partials, which launch_wgrad_sums adds up for every layer at once and writes
+// (not adds) to gWb[l][0 .. 5 cin cout + cout): dW (kKsize, cin, cout) then db.
 // h [R][cin] and dy [R][cout] bf16 packed rows, row words as in GemmArgs.
 // (cin, cout) in {(64, 64), (64, 4), (2, 64)}; partial: device scratch of
-// conv_wgrad_partial_bytes(R), 16-byte aligned.  Deterministic.
+// conv_wgrad_partial_bytes(cin, cout, R), 16-byte aligned.  Deterministic.
 bool conv_wgrad_fits(int cin, int cout);
-size_t conv_wgrad_partial_bytes(int64_t R);
+size_t conv_wgrad_partial_bytes(int cin, int cout, int64_t R);
 hipError_t launch_conv_wgrad(int cin, int cout, const uint16_t *h, const uint32_t *row_info, const uint16_t *dy,
-                             int64_t R, float *partial, float *gWb, hipStream_t st);
+                             int64_t R, float *partial, hipStream_t st);
+hipError_t launch_wgrad_sums(const float *const *partial, float *const *gWb, int64_t R, hipStream_t st);
 
 // Row words, owning series (optional) and layer-1 features of nSeries packed
 // series.  off: device offsets of those series into X; packed row of sample
@@ -105,9 +107,11 @@ hipError_t launch_pair_loss(const float *emb, const int32_t *pairs, const float 
                             float *demb, float *loss_sum, hipStream_t st);
 hipError_t launch_adamw(float *w, float *m, float *v, const float *g, int64_t n, float lr, float wd, int64_t step,
                         hipStream_t st);
-// bf16 operand copies of layer l's weights: wt [C_out][5 C_in] (forward),
-// wb [C_in][5 C_out] with wb[c][u C_out + n] = W[4-u][c][n] (backward data).
-hipError_t launch_weight_copies(const float *w, int cin, int cout, uint16_t *wt, uint16_t *wb, hipStream_t st);
+// bf16 operand copies of every layer's weights: wt[l] [C_out][5 C_in] (forward),
+// wb[l] [C_in][5 C_out] with wb[c][u C_out + n] = W[4-u][c][n] (backward data);
+// also zeroes n0 floats at zero0 and n1 at zero1.
+hipError_t launch_prepare(const float *const *w, uint16_t *const *wt, uint16_t *const *wb, float *zero0, int64_t n0,
+                          float *zero1, int64_t n1, hipStream_t st);
 hipError_t launch_fill(float *p, int64_t n, float v, hipStream_t st);
 
 // k-NN selection.

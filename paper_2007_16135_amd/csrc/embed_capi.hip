@@ -56,13 +56,12 @@ void take_weights(Carver &c, Weights &w)
     }
 }
 
-hipError_t make_weights(const float *params, const Weights &w, hipStream_t st)
+hipError_t make_weights(const float *params, const Weights &w, hipStream_t st, float *zero0 = nullptr, int64_t n0 = 0,
+                        float *zero1 = nullptr, int64_t n1 = 0)
 {
-    for (int l = 0; l < kLayers; ++l) {
-        hipError_t e = launch_weight_copies(params + layer_offset(l), kChan[l], kChan[l + 1], w.wt[l], w.wb[l], st);
-        if (e != hipSuccess) return e;
-    }
-    return hipSuccess;
+    const float *p[kLayers];
+    for (int l = 0; l < kLayers; ++l) p[l] = params + layer_offset(l);
+    return launch_prepare(p, w.wt, w.wb, zero0, n0, zero1, n1, st);
 }
 
 // Activations of a chunk of `rows` packed rows.  With `keep` every layer's
@@ -180,7 +179,7 @@ struct EmbedLayout {
     Acts a;
     float *emb, *demb;
     void *dy[3];  // bf16 gradients: [R][64] twice (ping-pong), [R][4]
-    float *wpart;  // per-workgroup weight-gradient partials
+    float *wpart[kLayers];  // per-workgroup weight-gradient partials
     size_t total;
 };
 
@@ -198,7 +197,8 @@ EmbedLayout embed_layout(char *base, int64_t n, int64_t total, int64_t maxlen, i
         L.dy[0] = c.take((size_t)total * 64 * 2);
         L.dy[1] = c.take((size_t)total * 64 * 2);
         L.dy[2] = c.take((size_t)total * kC4 * 2);
-        L.wpart = (float *)c.take(conv_wgrad_partial_bytes(total));
+        for (int l = 0; l < kLayers; ++l)
+            L.wpart[l] = (float *)c.take(conv_wgrad_partial_bytes(kChan[l], kChan[l + 1], total));
     }
     L.total = c.used;
     return L;
@@ -376,11 +376,11 @@ twed_status twed_embed_loss_grad(const float *params, const float *X, const int6
         if (e != hipSuccess) return fail_hip(e, what); \
     } while (0)
     TRY(hipMemcpyAsync(L.off, off, (size_t)(nSeries + 1) * 8, hipMemcpyHostToDevice, st), "offset upload");
-    TRY(make_weights(params, L.w, st), "weight copies");
+    // (the staged weight gradients write every element of grad)
+    const bool staged = conv_staged_enabled();
+    TRY(make_weights(params, L.w, st, L.demb, nSeries * kEmb, loss, 1), "weight copies");
     TRY(forward(params, L.w, a, X, L.off, (int)nSeries, 0, R, (int)maxlen, E, nullptr, nullptr, st), "forward");
-    TRY(launch_fill(L.demb, nSeries * kEmb, 0.f, st), "fill");
-    TRY(launch_fill(grad, kParamCount, 0.f, st), "fill");
-    TRY(launch_fill(loss, 1, 0.f, st), "fill");
+    if (!staged) TRY(launch_fill(grad, kParamCount, 0.f, st), "fill");
     TRY(launch_pair_loss(E, pairs, target, (int)nPairs, (int)nSeries, L.demb, loss, st), "pair loss");
     uint16_t *dy_out = (uint16_t *)L.dy[2];
     TRY(launch_pool_bwd(L.demb, a.row_info, a.row_series, R, dy_out, st), "pool backward");
@@ -390,8 +390,8 @@ twed_status twed_embed_loss_grad(const float *params, const float *X, const int6
         float *gW = grad + layer_offset(l);
         float *gb = gW + layer_w_count(l);
         // dW_l[(tap, c)][n] = sum_r h_l[r + tap - 2][c] dy_l[r][n], db_l[n] = sum_r dy_l[r][n]
-        if (conv_staged_enabled() && conv_wgrad_fits(cin, cout)) {
-            TRY(launch_conv_wgrad(cin, cout, inputs[l], a.row_info, dy_out, R, L.wpart, gW, st), "weight gradient");
+        if (staged) {
+            TRY(launch_conv_wgrad(cin, cout, inputs[l], a.row_info, dy_out, R, L.wpart[l], st), "weight gradient");
         } else {
             GemmArgs g;
             g.M = kKsize * cin;
@@ -429,6 +429,11 @@ twed_status twed_embed_loss_grad(const float *params, const float *X, const int6
         d.mask = inputs[l];
         TRY(launch_gemm(kOutBF16, d, 1, st), "data gradient");
         dy_out = dy_in;
+    }
+    if (staged) {
+        float *gWb[kLayers];
+        for (int l = 0; l < kLayers; ++l) gWb[l] = grad + layer_offset(l);
+        TRY(launch_wgrad_sums(L.wpart, gWb, R, st), "weight gradient sums");
     }
 #undef TRY
     return TWED_OK;

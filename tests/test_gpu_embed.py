@@ -473,3 +473,37 @@ def test_forward_windows_match_layers_bitwise(lens, generic_gemm):
     with generic_gemm:
         want = B.twed_embed_forward(vec, X, off).cpu().numpy()
     assert np.isfinite(got).all() and np.array_equal(got, want)
+
+
+@pytest.mark.parametrize("P", [1, 3, 4, 5, 16, 17, 65536, 65537, 70001])
+def test_pair_loss_over_workgroups(P):
+    # A wave takes several pairs, four waves add one sum, and above 65,536
+    # pairs the waves loop: pairs in no full wave or workgroup, and the loop.
+    # The loss is compared with its FP64 value at the returned embeddings; the
+    # sums of P / 16 workgroups round once per addition, each r to a few ulp of
+    # its two logarithms.  The gradient of tiled pairs is that of the first 16.
+    series = ragged_series(33)
+    vec, _ = random_params(33)
+    X, off = pack(series)
+    rng = np.random.default_rng(P)
+    base = np.stack([rng.integers(0, len(series), 16), rng.integers(0, len(series), 16)], axis=1)
+    pairs, t = np.resize(base, (P, 2)), np.resize(rng.uniform(0.0, 300.0, 16), P).astype(np.float32)
+    say(f"pair loss: {P} pairs")
+
+    def run(p, tt):
+        emb = torch.empty((len(series), 128), dtype=torch.float32, device="cuda")
+        loss, grad, _ = B.twed_embed_loss_grad(dev(vec), dev(X), off, dev(p, torch.int32), dev(tt), emb=emb)
+        return float(loss.item()), grad.cpu().numpy(), emb.cpu().numpy().astype(np.float64)
+
+    loss, grad, emb = run(pairs, t)
+    p = np.sqrt(((emb[pairs[:, 0]] - emb[pairs[:, 1]]) ** 2).sum(axis=1) + ocnn.EPS)
+    lp, lt = np.log1p(p), np.log1p(t.astype(np.float64))
+    r = lp - lt
+    u = 2.0 ** -24
+    bound = (2 * np.abs(r) * 8 * u * (lp + lt + 1)).mean() + (r * r).mean() * (20 + min(P // 16 + 1, 4096)) * u
+    assert abs(loss - (r * r).mean()) <= bound
+    if P % 16 == 0:
+        # scaled by 16 / P before BF16 operands, as a power of two: only the
+        # order of the atomic additions differs
+        _, g16, _ = run(base, t[:16])
+        assert rel_norm(grad, g16) < 1e-2
