@@ -85,6 +85,40 @@ twed_status sweep_long_listed_pairs(Prec prec, const CostParams &cp, const twed_
                                     int64_t nY, const int64_t *pairs, int64_t nPairs, void *state,
                                     int64_t maxlen, void *D, hipStream_t st);
 
+// Columns per lane of a strip sweep whose strips are all resident, one wave per
+// SIMD: the width in `widths` (ascending, 0 after the last) with the least
+// estimated time.  Strip s starts about 110 of its steps after strip s - 1 (the
+// lane skew of 64, a hand-over every 32 rows inside a group of four, one window
+// of 64 and its latency between groups) and a step of K columns takes about 1 +
+// q K of the time of its boundary work, so a sweep of nA rows by S strips takes
+// (nA + 110 S) (1 + q K).  q is a cell's arithmetic against that fixed part,
+// measured on sweeps of 100,000 x 5,000 and 20,000 x 20,000 samples: 0.24 for
+// 1-D samples, 0.36 / 0.62 for 3-D / 8-D L2 in FP32 costs, 0.69 / 0.75 in FP64.
+// (FP64 1-D, 30,000 x 30,000: 5.7 ms at the two columns chosen, 6.9 at one,
+// 7.4 at eight; 5,000 x 100,000: 5.2 ms at eight, 8.8 at two; 100,000 x 5,000:
+// 9.3 ms at one, 10.7 at two, 13.6 at four.)  0 when even the widest needs more
+// strips than `simds`.  fits(K): the kernel keeps to registers.
+template <typename Fits>
+int resident_strip_width(const int *widths, int64_t nA, int64_t nB, Prec prec, const CostParams &cp, int64_t simds,
+                         Fits &&fits)
+{
+    double q = prec == kF64 ? (cp.dimt == 1 ? 0.24 : 0.55 + 0.03 * cp.dimt) : 0.2 + 0.053 * cp.dimt;
+    if (cp.dimt > 1 && cp.pm == 2) q = 4.0;  // general p: a power per component
+    int best = 0;
+    double best_t = 0.0;
+    for (; *widths; ++widths) {
+        const int K = *widths;
+        const int64_t S = (nB + 64 * K - 1) / (64 * K);
+        if (S > simds) continue;
+        const double t = ((double)nA + 110.0 * (double)S) * (1.0 + q * K);
+        if ((best == 0 || t < best_t) && fits(K)) {
+            best = K;
+            best_t = t;
+        }
+    }
+    return best;
+}
+
 inline bool finite_nonneg(double v) { return std::isfinite(v) && v >= 0.0; }
 
 inline twed_status check_params(const twed_params *prm)

@@ -14,7 +14,7 @@ namespace {
 
 // Strip widths and group sizes compiled for the sibling recurrences.
 template <int DIMT, int K>
-constexpr bool kDpCompiled = (K == 1 || K == 2 || K == 8) && kStripCompiled<DIMT, K>;
+constexpr bool kDpCompiled = kStripCompiled<DIMT, K>;
 
 template <int REC, int DIMT>
 constexpr bool kDpDim = REC == kRecDtw || DIMT == 1;
@@ -56,7 +56,7 @@ hipError_t by_config(int rec, Prec prec, const CostParams &cp, int K, int G, Fn 
                         return hipErrorInvalidValue;
                     } else {
                         switch (G) {
-                        case 1: return fn.template operator()<CT, AT, DIMT, PM, KK, 1, REC>();
+                        case 4: return fn.template operator()<CT, AT, DIMT, PM, KK, 4, REC>();
                         case 8: return fn.template operator()<CT, AT, DIMT, PM, KK, 8, REC>();
                         default: return hipErrorInvalidValue;
                         }
@@ -65,6 +65,7 @@ hipError_t by_config(int rec, Prec prec, const CostParams &cp, int K, int G, Fn 
                 switch (K) {
                 case 1: return withK.template operator()<1>();
                 case 2: return withK.template operator()<2>();
+                case 4: return withK.template operator()<4>();
                 case 8: return withK.template operator()<8>();
                 default: return hipErrorInvalidValue;
                 }

@@ -46,12 +46,8 @@ struct Sweep {
     int K, G;
 };
 
-// The widest strip whose kernel keeps to registers and still leaves about
-// three strips for every four SIMDs (the rule of the pair sweep), in the
-// widest non-spilling group that leaves work for half the CUs.
 // The recurrence a sweep runs: kRecTwed, or a sibling (kRecDtw, kRecEdit,
-// kRecIndel; see twed_device.h), whose kernels exist for K in {1, 8} and G
-// in {1, 8} only.
+// kRecIndel; see twed_device.h), whose kernels exist for G in {4, 8} only.
 size_t sweep_scratch(int rec, bool dirs, Prec prec, const CostParams &cp, int K, int G)
 {
     if (dirs) return rec_dirs_scratch_bytes(rec, prec, cp, K, G);
@@ -64,46 +60,38 @@ int sweep_workers(int rec, bool dirs, Prec prec, const CostParams &cp, int K, in
     return rec == kRecTwed ? tile_max_workers(prec, cp, K, G) : dp_max_workers(rec, prec, cp, K, G);
 }
 
-// Move-recording sweeps (dirs) run strips of one column per lane.
-Sweep tile_sweep(int rec, int strip_k, int64_t nB, Prec prec, const CostParams &cp, bool dirs = false)
+// Strip width and group of a sweep of nA x nB cells: the pair sweep's rule
+// (resident_strip_width, groups of four, while the strips fit one wave per
+// SIMD; beyond that the widest strip that leaves three strips for every four
+// SIMDs, in groups of eight).  Move-recording sweeps (dirs) run strips of one
+// column per lane.
+Sweep tile_sweep(int rec, int strip_k, int64_t nA, int64_t nB, Prec prec, const CostParams &cp, bool dirs = false)
 {
     const bool sib = rec != kRecTwed && !dirs;
-    int K = 1;
-    if (dirs) {
-        K = 1;
-    } else if (strip_k > 0) {
-        K = strip_k;
-    } else {
-        const int64_t want = (int64_t)simds() * 3 / 4;
-        for (int k : {8, 4, 2}) {
-            if (sib && k == 4) continue;
-            const int64_t strips = (nB + 64 * k - 1) / (64 * k);
-            if (strips >= want && sweep_scratch(rec, dirs, prec, cp, k, 1) == 0) {
-                K = k;
-                break;
+    const int64_t n_simds = simds();
+    auto fits = [&](int K, int G) { return sweep_scratch(rec, dirs, prec, cp, K, G) == 0; };
+    static const int any[] = {1, 2, 4, 8, 0};
+    const int one[] = {dirs ? 1 : strip_k, 0};
+    int G = 4;
+    int K = resident_strip_width(one[0] > 0 ? one : any, nA, nB, prec, cp, n_simds, [&](int k) { return fits(k, 4); });
+    if (K == 0) {
+        K = one[0] > 0 ? one[0] : 1;
+        if (one[0] <= 0) {
+            for (int k : {8, 4, 2}) {
+                if ((nB + 64 * k - 1) / (64 * k) * 4 >= n_simds * 3 && (fits(k, 8) || fits(k, 4))) {
+                    K = k;
+                    break;
+                }
             }
         }
-    }
-    // Groups: in-group handoffs go through LDS, which shortens the pipeline,
-    // so the widest group that still leaves work for half the CUs; a
-    // move-recording sweep of one block is latency-bound, not width-bound,
-    // and takes the widest group that has a few groups to pipeline.
-    const int64_t nStrips = (nB + 64 * K - 1) / (64 * K);
-    const int64_t cus = std::max(1, simds() / 4);
-    const int64_t want_groups = dirs ? 2 : std::max<int64_t>(1, cus / 2);
-    int G = 1;
-    for (int g : {8, 4}) {
-        if (sib && g != 8) continue;
-        if ((nStrips + g - 1) / g >= want_groups && nStrips >= g && sweep_scratch(rec, dirs, prec, cp, K, g) == 0) {
-            G = g;
-            break;
-        }
+        if (fits(K, 8)) G = 8;
+        else if (!fits(K, 4) && !sib) G = 1;
     }
     // TWED_WAVEFRONT_GROUP (1, 4 or 8) overrides the group of plain TWED
     // tile sweeps for tuning runs
     if (const char *env = std::getenv("TWED_WAVEFRONT_GROUP")) {
         const int g = std::atoi(env);
-        if (!sib && !dirs && (g == 1 || g == 4 || g == 8) && sweep_scratch(rec, dirs, prec, cp, K, g) == 0) G = g;
+        if (!sib && !dirs && (g == 1 || g == 4 || g == 8) && fits(K, g)) G = g;
     }
     return Sweep{K, G};
 }
@@ -142,7 +130,7 @@ twed_status run_tile(int rec, Prec prec, const CostParams &cp, Sweep sw, const v
     w.out = out;
     w.dump = nullptr;
     w.group = sw.G;
-    w.sub_shift = 4;
+    w.sub_shift = kSubShift;
     const int workers = sweep_workers(rec, t.dirs != nullptr, prec, cp, sw.K, sw.G);
     if (workers <= 0) return fail(TWED_ERR_DEVICE, "occupancy query failed");
     w.grid = (int)std::min<int64_t>((w.nStrips + sw.G - 1) / sw.G, workers);
@@ -174,13 +162,13 @@ PathGeometry path_geometry(int rec, const twed_params *prm, int64_t nA, int64_t 
 {
     PathGeometry g{};
     const int64_t want = block > 0 ? block : kDefaultBlock;
-    g.fwd = tile_sweep(rec, prm->strip_k, nB, prec, cp);
+    g.fwd = tile_sweep(rec, prm->strip_k, nA, nB, prec, cp);
     const int64_t W = 64 * (int64_t)g.fwd.K;
     g.H = std::max<int64_t>(64, want);
     g.Wc = (std::max(want, W) + W - 1) / W * W;
     g.nr = (nA - 1) / g.H;
     g.nc = (nB - 1) / g.Wc;
-    g.blk = tile_sweep(rec, 0, std::min(g.Wc, nB), prec, cp, true);
+    g.blk = tile_sweep(rec, 0, std::min(g.H, nA), std::min(g.Wc, nB), prec, cp, true);
     return g;
 }
 
@@ -467,7 +455,7 @@ twed_status twed_pair_tile(const void *A, const void *TA, int64_t nA, const void
     t.bottom = bottom;
     t.right = right;
     t.dummy = b.dummy;
-    return run_tile(kRecTwed, prec, cp, tile_sweep(kRecTwed, prm->strip_k, nBt, prec, cp), b.rowsA, b.rowsB, nAt,
+    return run_tile(kRecTwed, prec, cp, tile_sweep(kRecTwed, prm->strip_k, nAt, nBt, prec, cp), b.rowsA, b.rowsB, nAt,
                     nBt, b, t, corner ? (void *)corner : b.tmp, st);
 }
 
@@ -538,7 +526,7 @@ twed_status twed_dp(int32_t kind, const void *A, int64_t nA, const void *B, int6
         t.top = row0;
         t.left = col0;
     }
-    s = run_tile(rec, prec, cp, tile_sweep(rec, prm->strip_k, nB, prec, cp), b.rowsA, b.rowsB, nA, nB, b, t, out, st);
+    s = run_tile(rec, prec, cp, tile_sweep(rec, prm->strip_k, nA, nB, prec, cp), b.rowsA, b.rowsB, nA, nB, b, t, out, st);
     if (s != TWED_OK) return s;
     if (kind == TWED_DP_LCS && (e = launch_lcs_finish(out, nA, nB, st)) != hipSuccess) return fail_hip(e, "LCS");
     return TWED_OK;

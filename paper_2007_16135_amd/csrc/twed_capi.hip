@@ -64,23 +64,42 @@ int device_simds()
     return cus * 4;
 }
 
-// Columns per lane of the wavefront sweep: the widest strip that still
-// leaves about three strips for every four SIMDs, and whose kernel keeps
-// everything in registers (wide strips of high-dimensional or general-Lp
-// sweeps would spill).  Narrow strips fill more SIMDs but lengthen the
-// pipeline (each strip starts 64 + 16 steps after the one before it) and
-// pay the per-step work for fewer cells: on the 3-D n = 1e5 pair, strips of
-// two columns (782 strips) sweep 1.36x faster in FP64 than strips of one
-// (1,563 strips, two waves on some SIMDs).
-int choose_k(const twed_params *prm, int64_t nB, Prec prec, const CostParams &cp)
+// A kernel with at most this much scratch per lane keeps its step loop in
+// registers (a few words outside it may be spilled).
+constexpr size_t kScratchAllowed = 32;
+
+bool pair_kernel_fits(Prec prec, const CostParams &cp, int K, int G)
 {
-    if (prm->strip_k > 0) return prm->strip_k;
-    const int64_t want = (int64_t)device_simds() * 3 / 4;
-    for (int k : {8, 4, 2}) {
-        const int64_t strips = (nB + 64 * k - 1) / (64 * k);
-        if (strips >= want && wavefront_scratch_bytes(prec, cp, k, 1) == 0) return k;
+    return wavefront_scratch_bytes(prec, cp, K, G) <= kScratchAllowed;
+}
+
+// Columns per lane and strips per workgroup of the wavefront sweep.  While the
+// strips fit one wave per SIMD, groups of four (a wave on each SIMD of a compute
+// unit) of the width that resident_strip_width picks.  Beyond that the widest
+// strip whose kernel keeps to registers (wide strips of high-dimensional or
+// general-Lp sweeps would spill) that still gives three strips for every four
+// SIMDs, in groups of eight where those keep to registers (eight waves put two
+// on each SIMD, which halves the registers a lane may hold), else of four.
+void choose_layout(const twed_params *prm, int64_t nA, int64_t nB, Prec prec, const CostParams &cp, int *K, int *G)
+{
+    const int64_t simds = device_simds();
+    static const int widths[] = {1, 2, 4, 8, 0};
+    const int one[] = {prm->strip_k, 0};
+    *G = 4;
+    *K = resident_strip_width(prm->strip_k > 0 ? one : widths, nA, nB, prec, cp, simds,
+                              [&](int k) { return pair_kernel_fits(prec, cp, k, 4); });
+    if (*K > 0) return;
+    *K = prm->strip_k > 0 ? prm->strip_k : 1;
+    if (prm->strip_k <= 0) {
+        for (int k : {8, 4, 2}) {
+            if ((nB + 64 * k - 1) / (64 * k) * 4 >= simds * 3 && wavefront_scratch_bytes(prec, cp, k, 1) == 0) {
+                *K = k;
+                break;
+            }
+        }
     }
-    return 1;
+    if (pair_kernel_fits(prec, cp, *K, 8)) *G = 8;
+    else if (!pair_kernel_fits(prec, cp, *K, 4)) *G = 1;
 }
 
 // Words after the per-strip flags in the zeroed region: work ticket, wait
@@ -218,7 +237,10 @@ twed_status plan_pair_sweep(Prec prec, const CostParams &cp, const twed_params *
 {
     SweepChoice tuned{};
     const bool have_tuned = !force && !dump && prm->strip_k == 0 && tuned_choice(prec, cp, nB, &tuned);
-    int K = force ? force->K : (have_tuned ? tuned.K : choose_k(prm, nB, prec, cp));
+    int K = 0, G = 0;
+    choose_layout(prm, nA, nB, prec, cp, &K, &G);
+    if (force) K = force->K;
+    else if (have_tuned) K = tuned.K;
     if (dump) {
         // cell dumps exist for narrow strips only (a validation aid)
         if (prm->strip_k > 2) return fail(TWED_ERR_UNSUPPORTED, "twed_pair_matrix takes strip_k 0, 1 or 2");
@@ -228,27 +250,18 @@ twed_status plan_pair_sweep(Prec prec, const CostParams &cp, const twed_params *
     plan->s1 = 0;
     plan->nStrips = (nB + 64 * K - 1) / (64 * K);
     // Strips per workgroup: in-group handoffs go through LDS, one in G
-    // through global memory.  The widest group that still leaves about
-    // three groups for every four CUs and whose kernel keeps to registers
-    // (eight waves put two on each SIMD, which halves the registers a lane
-    // may hold: too few for the widest high-dimensional strips); cell dumps
-    // use single-wave groups.
-    // TWED_WAVEFRONT_GROUP
-    // (1, 4 or 8) and TWED_WAVEFRONT_SUB (in-group handoff rows: 8, 16 or 32)
-    // override the choices for tuning runs.
-    const int64_t cus = std::max(1, device_simds() / 4);
-    plan->G = 1;
-    for (int G : {8, 4})
-        if (plan->nStrips * 4 >= (int64_t)G * cus * 3 && wavefront_scratch_bytes(prec, cp, K, G) == 0) {
-            plan->G = G;
-            break;
-        }
+    // through global memory; cell dumps use single-wave groups.
+    // TWED_WAVEFRONT_GROUP (1, 4 or 8) and TWED_WAVEFRONT_SUB (in-group handoff
+    // rows: 8, 16 or 32) override the choices for tuning runs.  A handoff every
+    // 32 rows beats 16 by 1 .. 3% and 8 by 8 .. 15% at every size measured (200
+    // to 10^6 samples): each costs the waves a poll and two fences.
+    plan->G = G;
     if (dump) plan->G = 1;
     if (const char *env = std::getenv("TWED_WAVEFRONT_GROUP")) {
         const int G = std::atoi(env);
         if ((G == 1 || G == 4 || G == 8) && !dump) plan->G = G;
     }
-    plan->sub_shift = 4;
+    plan->sub_shift = kSubShift;
     if (const char *env = std::getenv("TWED_WAVEFRONT_SUB")) {
         const int v = std::atoi(env);
         if (v == 8 || v == 16 || v == 32) plan->sub_shift = v == 8 ? 3 : (v == 16 ? 4 : 5);
@@ -938,16 +951,16 @@ static twed_status twed_pair_tune_body(const void *A, const void *TA, int64_t nA
         if (ev0) hipEventDestroy(ev0);
         return fail_hip(e, "event create");
     }
-    SweepChoice best{0, 0, 4};
+    SweepChoice best{0, 0, kSubShift};
     float best_ms = 0.f;
     twed_params p1 = *prm;
     p1.strip_k = 0;
     for (int K : {8, 4, 2, 1}) {
-        if (wavefront_scratch_bytes(prec, cp, K, 1) != 0) continue;
+        if (!pair_kernel_fits(prec, cp, K, 1)) continue;
         const int64_t strips = (nB + 64 * K - 1) / (64 * K);
         for (int G : {8, 4, 1}) {
-            if (G > 1 && (strips < 2 * G || wavefront_scratch_bytes(prec, cp, K, G) != 0)) continue;
-            const SweepChoice c{K, G, 4};
+            if (G > 1 && !pair_kernel_fits(prec, cp, K, G)) continue;
+            const SweepChoice c{K, G, kSubShift};
             // restaging A zeroes the flags and the ticket for this run
             e = launch_stage(prec, cp, A, TA, nullptr, 1, rows, rows, rows + 1, L.rowsA, flags, L.zero_words, st);
             if (e == hipSuccess) e = hipEventRecord(ev0, st);

@@ -71,6 +71,8 @@ struct WavefrontArgs {
     int sub_shift;      // in-group handoff every 1 << sub_shift rows (3, 4 or 5)
     int s1;             // two strip widths (launch_wavefront_mixed): strips before s1 hold K columns per lane
 };
+// In-group handoff interval of a sweep: every 1 << kSubShift rows.
+constexpr int kSubShift = 5;
 hipError_t launch_wavefront(Prec prec, const CostParams &cp, int K, const WavefrontArgs &a, hipStream_t st);
 // Strips of two widths (wavefront_mixed.hip): layout m sweeps strips 0 .. a.s1-1
 // with kMixedLayouts[m].wide columns per lane and the others with .narrow,
@@ -121,8 +123,8 @@ int tile_max_workers(Prec prec, const CostParams &cp, int K, int G);
 // the inputs or set to the +inf pad); launched after every tile sweep.
 hipError_t launch_tile_edges(int64_t nA, int64_t nB, const TileArgs &t, hipStream_t st);
 // The tile sweep on a sibling recurrence (dp.hip; rec: 1 DTW, 2 edit
-// distance, 3 indel distance), strips of K = 1, 2 or 8 columns per lane,
-// groups of G = 1 or 8 strips; other configurations return hipErrorInvalidValue /
+// distance, 3 indel distance), strips of K = 1, 2, 4 or 8 columns per
+// lane, groups of G = 4 or 8 strips; other configurations return hipErrorInvalidValue /
 // (size_t)-1 / 0.
 hipError_t launch_dp(int rec, Prec prec, const CostParams &cp, int K, const WavefrontArgs &a, const TileArgs &t,
                      hipStream_t st);

@@ -6,7 +6,6 @@
 
 namespace twed {
 
-
 // Polls of a predecessor's progress word before a wave gives up (tens of
 // seconds either way: an LDS poll takes about 0.1 us with its sleep, a
 // global one a few us).
@@ -28,14 +27,36 @@ struct alignas(2 * sizeof(AT)) Pair2 {
 // 32; a kernel argument).
 constexpr int kWindow = 64;
 // Rows of one in-group boundary kept in LDS (power of two), plus one slot
-// that absorbs the writes of lanes without a row.
+// that absorbs the writes of lanes without a row.  Row r sits at slot
+// (r - 1) mod 128: the rows a sub-chunk of steps reads or writes then fill
+// consecutive slots without a wrap (sub-chunks start at multiples of their
+// length, and rows t + 1 come in and rows t - 63 go out at step t), so a step
+// reaches them at a constant offset from an address kept in a register.
 constexpr int kRing = 128;
+__host__ __device__ constexpr int ring_slot(int r) { return (r - 1) & (kRing - 1); }
+// Most steps between two updates of the boundary addresses.
+constexpr int kMaxUnroll = 4;
 
-template <typename AT, int G>
+// Rows of A reach the lanes through LDS: every 64 steps lane l of a wave loads
+// row t + l and writes it to the wave's ring, and at step t lane l reads row
+// t - l.  The ring holds 64-row chunks c - 1 and c, always contiguous (chunk c
+// even at rows 64 .. 127, odd at rows 128 .. 191 and again at 0 .. 63), so a
+// step needs no address wrap.  Read from global memory by every lane at every
+// step, a row came 64 times through the L1 (2 KB per wave and step for 32-byte
+// rows, at 64 B per cycle) and its latency, three steps of a narrow strip, was
+// often not hidden: 3-D FP32 strips took 150 ns per step whatever their width.
+// Samples whose rings do not fit the LDS beside the rest keep the global reads.
+template <typename CT, int DIMT, int G>
+constexpr bool kRowRing = (3 * kWave + 1) * Row<CT, DIMT>::kStride * (int)sizeof(CT) * G <= 128 * 1024;
+
+template <typename CT, typename AT, int DIMT, int G>
 struct GroupShared {
+    alignas(16) CT rows[G][kRowRing<CT, DIMT, G> ? (3 * kWave + 1) * Row<CT, DIMT>::kStride : 1];
     Pair2<AT> ring[G > 1 ? G - 1 : 1][kRing + 1];  // boundary of wave w, read by wave w+1
     Pair2<AT> in_stage[kWindow];                   // wave 0's left boundary, one global window
+    Pair2<AT> in_next[kWindow];                    // the next window, when it is there early
     Pair2<AT> out_stage[kRing + 1];                // wave G-1's right boundary before it goes out
+    Pair2<AT> dummy[kWave + kMaxUnroll];           // takes the boundary writes of lanes 0 .. 62
     uint32_t prod[G];                              // rows of that boundary published
     uint32_t cons[G];                              // rows of wave w's left boundary consumed
     uint32_t ticket[G];                            // ticket value seen by each wave (wave 0's is the claim)
@@ -111,15 +132,21 @@ constexpr bool kStripCompiled = DIMT <= 16 || K <= 2;
 // One strip of 64*K columns swept by one wave.  Its left boundary (DP and X =
 // DP + e of column c0-1, per row) comes from the previous strip: through LDS
 // when that strip belongs to the same workgroup (handoff every kSub rows,
-// workgroup-scope release/acquire), through a global slot and flag
-// otherwise (every kWindow rows, agent scope).  Its right boundary goes the
+// workgroup-scope release/acquire; kSub = 1 << sub_shift), through a global
+// slot and flag otherwise (every kWindow rows, agent scope).  Its right boundary goes the
 // same two ways to the next strip.
 //
-// rowsA points at row 0 of A and must stay readable from row -64 to row
-// nA + 63 + the prefetch distance (the staging pads the buffer with kRowPad
-// rows before and kRowPadTail after): lanes that have not started yet, or
-// have finished, read rows outside 1..nA and compute values nobody uses, so
-// the row address needs no clamp.
+// rowsA points at row 0 of A, with kRowPad rows before it and kRowPadTail after
+// row nA.  Lanes that have not started yet, or have finished, sweep rows
+// outside 1..nA (with the ring, rows of zeros before row 0) and compute values
+// nobody uses, so the row address needs no clamp.
+//
+// What bounds a step: with one wave on a SIMD, everything the step issues, so
+// the loop holds no branch, no address arithmetic beyond one update every four
+// steps and no scalar test; the cells themselves are the floor.  Before this
+// form a step of one FP64 1-D column took 178 ns, now 100; with the width rule
+// 30,000 x 30,000 samples went from 10.5 to 4.9 ms, 1,000 x 1,000 from 355 to
+// 181 us, 100,000 x 100,000 3-D in FP32 from 29.6 to 22.2 ms.
 //
 // A tile sweep (TILE) starts from a given top row and left column instead of
 // the pad row and column.  A lane processes rows 0 and below before its
@@ -127,7 +154,7 @@ constexpr bool kStripCompiled = DIMT <= 16 || K <= 2;
 // row, and in a tile the lane loads its top-row cells at the step where it
 // sits on row 0, so that row 1 starts from them.
 template <typename CT, typename AT, int DIMT, int PM, int K, int G, bool DUMP, bool TILE, int REC, bool DIRS>
-__device__ __forceinline__ void sweep_strip(GroupShared<AT, G> &sh, int w, int g, int s, int cbase,
+__device__ __forceinline__ void sweep_strip(GroupShared<CT, AT, DIMT, G> &sh, int w, int g, int s, int cbase,
                                             const CT *__restrict__ rowsA,
                                             const CT *__restrict__ rowsB, int nA, int nB, const CostArgs<CT> &ca,
                                             Pair2<AT> *bnd, uint32_t *flags, uint32_t *err, int nStrips, CT beta,
@@ -140,9 +167,6 @@ __device__ __forceinline__ void sweep_strip(GroupShared<AT, G> &sh, int w, int g
     constexpr int W = kWave * K;
     const int lane = threadIdx.x & (kWave - 1);
     const AT INF = pinf<AT>();
-    // Row t - lane of A, the row lane `lane` works on at step t: a pointer
-    // that advances by one row per step (a 64-bit add, no multiply).
-    const CT *row_ptr = rowsA - (ptrdiff_t)lane * S;
     // ---- columns of this lane (the strip's first column is 1 + cbase)
     const int c0 = 1 + cbase + lane * K;
     Lane<CT, AT, DIMT, K> L;
@@ -200,76 +224,95 @@ __device__ __forceinline__ void sweep_strip(GroupShared<AT, G> &sh, int w, int g
     // lstar hold columns beyond nB): the result is then in that lane's
     // registers, and the step loop carries no test for it.
     const int T_run = result_strip ? nA + lstar + 1 : T;
-    // Rows of A are loaded kAhead steps before their use, from a ring of
-    // kAhead + 1 rows (kAhead + 1 divides every sub-chunk of 8, 16 or 32
-    // steps).  Narrow strips of small samples load three rows ahead.  So do
-    // pair sweeps of wide strips whose ring of rows stays small next to the
-    // lane's columns (at most 96 registers for the K columns' rows), e.g. 8-D
-    // FP32 rows: consecutive groups on one XCD read rows far apart, so a row
-    // often comes from the Infinity Cache, and one step of even eight
-    // columns does not hide that latency.  Tile sweeps of wide strips load
-    // one row ahead (a deeper ring pushed the tile kernels of eight-wave
-    // groups past 256 registers), and so do large samples.
-    constexpr int kRowRegs = Row<CT, DIMT>::kStride * (int)sizeof(CT) / 4;
-    constexpr int kAhead = (DIMT <= 8 && (K <= 2 || (!TILE && kRowRegs * K <= 64))) ? 3 : 1;
-    // lane 0 prefetches up to row nA + 63 + kAhead: inside the zero rows
-    // that end every packed buffer
-    static_assert(kWave - 1 + kAhead <= kRowPadTail, "row prefetch runs past the buffer padding");
-    Row<CT, DIMT> cur, nxt;
-    Row<CT, DIMT> ring[kAhead + 1];
-    if constexpr (kAhead == 1) {
-        load_row<CT, DIMT>(row_ptr, 0, cur);
-    } else {
+    // The row of the next step is read one step ahead: from the wave's ring in
+    // LDS, or from global memory (large samples).
+    // (Wide strips of large samples, whose columns fill the registers, have none
+    // left for the ring's loads.)
+    constexpr bool RR = kRowRing<CT, DIMT, G> && S * (int)sizeof(CT) / 4 * K <= 96;
+    constexpr int V = 16 / (int)sizeof(CT);
+    typedef CT vec __attribute__((ext_vector_type(V)));
+    CT *const rows_lds = &sh.rows[w][0];
+    vec fetched[S / V];
+    auto fetch = [&](int t) {  // rows t .. t + 63, a row per lane (those past nA + 64 repeat a padding row)
+        const int r = t + lane < nA + kRowPad ? t + lane : nA + kRowPad;
+        const vec *p = reinterpret_cast<const vec *>(rowsA + (ptrdiff_t)r * S);
 #pragma unroll
-        for (int k = 0; k < kAhead; ++k) load_row<CT, DIMT>(row_ptr, k, ring[k]);
+        for (int v = 0; v < S / V; ++v) fetched[v] = p[v];
+    };
+    auto put = [&](int slot) {
+        vec *p = reinterpret_cast<vec *>(rows_lds + (slot + lane) * S);
+#pragma unroll
+        for (int v = 0; v < S / V; ++v) p[v] = fetched[v];
+    };
+    static_assert(kRowPad <= kRowPadTail && kWave <= kRowPadTail, "rows up to nA + 64 are read");
+    Row<CT, DIMT> cur, nxt;
+    const CT *row_at;  // row t - lane, the row lane `lane` works on at step t
+    if constexpr (RR) {
+        // lanes that have not reached row 0 sweep rows of zeros
+#pragma unroll
+        for (int v = 0; v < S / V; ++v) fetched[v] = vec{};
+        put(0);
+        fetch(0);
+        row_at = rows_lds;
+    } else {
+        row_at = rowsA - (ptrdiff_t)lane * S;
+        load_row<CT, DIMT>(row_at, 0, cur);
     }
-    row_ptr += kAhead * S;  // row kAhead - lane: the first prefetch
     // Lane 0's left operands of the next step come from one LDS read at a
     // wave-uniform address (a broadcast: no cross-lane moves, no lane
     // selection): from the ring of the previous wave of the group, or from
     // in_stage, which holds one window of the global slot (or +inf: the pad
     // column of the first strip).  Lane 63's output of every step -- the
-    // strip's right boundary -- is written by that lane alone to the ring of
-    // the next wave, or to out_stage when it leaves the group through global
-    // memory, from where whole windows are copied out.
+    // strip's right boundary -- goes to the ring of the next wave, or to
+    // out_stage when it leaves the group through global memory, from where
+    // whole windows are copied out.  Every lane executes that store, the others
+    // into cells nobody reads: masking them off took five scalar instructions
+    // and a branch per step, which a strip alone on its SIMD pays for in full.
     const bool has_in = in_global || in_lds;
     if (!has_in) sh.in_stage[lane] = Pair2<AT>{INF, INF};
-    // boundary row t + 1 sits at in_src[(t + in_add) & in_mask]: ring slot
-    // (t + 1) mod 128, or in_stage slot t - wb = t mod 64
-    const Pair2<AT> *const in_src = in_lds ? &sh.ring[w > 0 ? w - 1 : 0][0] : &sh.in_stage[0];
-    const int in_add = in_lds ? 1 : 0;
+    // boundary row t + 1 sits at in_src[t & in_mask]: ring slot t mod 128, or
+    // in_stage slot t mod 64
     const int in_mask = in_lds ? kRing - 1 : kWindow - 1;
+    const Pair2<AT> *const in_src = in_lds ? &sh.ring[w > 0 ? w - 1 : 0][0] : &sh.in_stage[0];
     Pair2<AT> *const out_ring = out_lds ? &sh.ring[w < G - 1 ? w : 0][0] : &sh.out_stage[0];
 
     // The next global window is fetched ahead when it is already published:
     // its flag is read at the start of the window's second-to-last sub-chunk
     // (the load completes behind that sub-chunk's steps), checked at the last
-    // one, and the window's rows are loaded there into registers, to be
-    // staged in LDS at the next window's start (their latency, too, hides
-    // behind a sub-chunk).  Otherwise the window start waits for the flag.
-    // (Single-strip groups, where every strip hands over through global
-    // memory, wait at each window start: fetching ahead there kept the
-    // window's rows in scratch memory.)
-    constexpr bool kAheadFetch = G > 1;
+    // one, and the window's rows go to in_next there.  Otherwise the window
+    // start waits for the flag.  (Rows held in registers until the window
+    // starts lengthened the step loop: the 8-D pair of 10^6 samples ran in 896
+    // ms instead of 884.)
     const int q_last = (kWindow >> sub_shift) - 1;
     uint32_t ahead_flag = 0;
     bool ahead = false;
-    Pair2<AT> ahead_rows{};
     for (int t0 = 0; t0 < T_run; t0 += kSub) {
         const int q = (t0 >> sub_shift) & ((kWindow >> sub_shift) - 1);  // sub-chunk within the window
         const int wb = t0 - q * kSub;                          // window start
         const int steps = T_run - t0 < kSub ? T_run - t0 : kSub;
         const bool flagged = !TILE || s > 0;  // a tile's left column is there from the start
+        if (RR && q == 0) {
+            // (LDS accesses of one wave complete in order; the fences keep the
+            // compiler from moving a row read across these writes)
+            const int odd = (t0 / kWave) & 1;
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            put(odd ? 2 * kWave : kWave);
+            if (odd) put(0);
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            if (t0 + kWave < T_run) fetch(t0 + kWave);
+            row_at = rows_lds + ((odd ? 2 * kWave : kWave) - lane) * S;
+            load_row<CT, DIMT>(row_at, 0, cur);
+        }
         if (in_global && q == 0) {
             if (ahead) {
-                sh.in_stage[lane] = ahead_rows;
+                sh.in_stage[lane] = sh.in_next[lane];
             } else {
                 if (flagged) {
                     const uint32_t need = (uint32_t)(t0 + kWindow < nA ? t0 + kWindow : nA);
                     wait_progress<false>(in_flag, need, err);
                     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
                 }
-                // rows t0 + 1 .. t0 + 64 of the boundary: lane l's row to slot l
+                // rows t0 + 1 .. t0 + 64 of the boundary
                 const int rr = t0 + 1 + lane < nA ? t0 + 1 + lane : nA;
                 sh.in_stage[lane] = in_slot[rr];
             }
@@ -277,15 +320,15 @@ __device__ __forceinline__ void sweep_strip(GroupShared<AT, G> &sh, int w, int g
         }
         // (the flag's value is taken wave-uniform only where it is used, so
         // the wave does not wait for the load where it is issued)
-        if (kAheadFetch && in_global && flagged && q_last > 0 && q == q_last - 1)
+        if (in_global && flagged && q_last > 0 && q == q_last - 1)
             ahead_flag = __hip_atomic_load(in_flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (kAheadFetch && in_global && q == q_last && wb + kWindow < T_run) {
+        if (in_global && q == q_last && wb + kWindow < T_run) {
             const int nb0 = wb + kWindow;  // the next window's start
             const uint32_t need = (uint32_t)(nb0 + kWindow < nA ? nb0 + kWindow : nA);
             if (!flagged || (q_last > 0 && wave_uniform(ahead_flag) >= need)) {
                 if (flagged) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
                 const int rr = nb0 + 1 + lane < nA ? nb0 + 1 + lane : nA;
-                ahead_rows = in_slot[rr];
+                sh.in_next[lane] = in_slot[rr];
                 ahead = true;
             }
         }
@@ -303,18 +346,26 @@ __device__ __forceinline__ void sweep_strip(GroupShared<AT, G> &sh, int w, int g
             if (last_w > kRing) wait_progress<true>(&sh.cons[w + 1], (uint32_t)(last_w - kRing), err);
         }
 
-        // One step: sweep row t - lane with `use`, prefetch row t + kAhead -
-        // lane into `fill`.  Steps rotate the row buffers, so the prefetched
-        // row never has to be copied.  SP (tile sweeps): this sub-chunk holds
-        // a step where top-row cells enter or boundary cells leave; the other
-        // sub-chunks run without testing for them at every step.
-        auto step = [&]<bool SP>(int i, Row<CT, DIMT> &use, Row<CT, DIMT> &fill) {
+        // This sub-chunk's first boundary cells: row t0 + 1 in, row t0 - 63 out
+        // (rows -63 .. 0 of the first 64 steps land in the slots of rows 65 ..
+        // 128, which are written again with those rows, at steps 128 .. 191,
+        // before anyone may read them).
+        const Pair2<AT> *in_at = in_src + (t0 & in_mask);
+        Pair2<AT> *out_at = has_out && lane == kWave - 1 ? out_ring + ring_slot(t0 - (kWave - 1)) : &sh.dummy[lane];
+        const int out_step = has_out && lane == kWave - 1 ? 1 : 0;
+        // One step: sweep row t - lane with `use`, read row t + 1 - lane into
+        // `fill`; OFF is the step's place in its unrolled run.  Steps alternate
+        // the row buffers, so the row read ahead never has to be copied.  SP
+        // (tile sweeps): this sub-chunk holds a step where top-row cells enter
+        // or boundary cells leave; the other sub-chunks run without testing for
+        // them at every step.
+        auto step = [&]<bool SP, int OFF>(int i, Row<CT, DIMT> &use, Row<CT, DIMT> &fill) {
+            static_assert(OFF < kMaxUnroll, "sh.dummy has room for this many");
             const int t = t0 + i;
-            load_row<CT, DIMT>(row_ptr, 0, fill);  // row t + kAhead - lane
-            row_ptr += S;
+            load_row<CT, DIMT>(row_at, OFF + 1, fill);
             // boundary row t + 1, which lane 0 meets at the next step (read
             // before the cells so that its latency hides behind them)
-            const Pair2<AT> nb = in_src[(t + in_add) & in_mask];
+            const Pair2<AT> nb = in_at[OFF];
 
             AT left = sh_l, xl;
             if constexpr (TILE) {
@@ -398,41 +449,29 @@ __device__ __forceinline__ void sweep_strip(GroupShared<AT, G> &sh, int w, int g
             sh_xo = sh_x;
             sh_l = shift_in(left, nb.dp);
             sh_x = shift_in(xl, nb.x);
-            if (has_out && lane == kWave - 1) {
-                // Lane 63 holds row t - 63 of the strip's right boundary.
-                // Rows -63 .. 0 of the first 64 steps land in the slots of
-                // rows 65 .. 128, which are written again with those rows
-                // (steps 128 .. 191) before anyone may read them.
-                out_ring[(t - (kWave - 1)) & (kRing - 1)] = Pair2<AT>{left, xl};
-            }
+            out_at[OFF] = Pair2<AT>{left, xl};  // (lane 63: row t - 63 of the strip's right boundary)
+            // Wide strips fill the SIMD by themselves; steps mixed with their
+            // neighbours would only cost registers.
+            if constexpr (S * (int)sizeof(CT) / 4 * K > 96) __builtin_amdgcn_sched_barrier(0);
+        };
+        auto advance = [&](int n) {
+            row_at += n * S;
+            in_at += n;
+            out_at += n * out_step;
         };
         auto run = [&]<bool SP>() {
             int i = 0;
-            if constexpr (kAhead == 1) {
-                for (; i + 1 < steps; i += 2) {
-                    step.template operator()<SP>(i, cur, nxt);
-                    step.template operator()<SP>(i + 1, nxt, cur);
-                }
-                if (i < steps) {
-                    step.template operator()<SP>(i, cur, nxt);
-                    cur = nxt;
-                }
-            } else {
-                // ring[k] holds row t + k (k < kAhead) at the start of each
-                // run of kAhead + 1 steps; sub-chunks are multiples of that
-                // run except at the end of the sweep, where the ring is
-                // shifted step by step
-                constexpr int R = kAhead + 1;
-                for (; i + R <= steps; i += R) {
-#pragma unroll
-                    for (int k = 0; k < R; ++k)
-                        step.template operator()<SP>(i + k, ring[k], ring[(k + kAhead) % R]);
-                }
-                for (; i < steps; ++i) {
-                    step.template operator()<SP>(i, ring[0], ring[kAhead]);
-#pragma unroll
-                    for (int k = 0; k < kAhead; ++k) ring[k] = ring[k + 1];
-                }
+            for (; i + kMaxUnroll <= steps; i += kMaxUnroll) {
+                step.template operator()<SP, 0>(i, cur, nxt);
+                step.template operator()<SP, 1>(i + 1, nxt, cur);
+                step.template operator()<SP, 2>(i + 2, cur, nxt);
+                step.template operator()<SP, 3>(i + 3, nxt, cur);
+                advance(kMaxUnroll);
+            }
+            for (; i < steps; ++i) {  // the end of the sweep
+                step.template operator()<SP, 0>(i, cur, nxt);
+                cur = nxt;
+                advance(1);
             }
         };
         if constexpr (TILE) {
@@ -476,7 +515,7 @@ __device__ __forceinline__ void sweep_strip(GroupShared<AT, G> &sh, int w, int g
             const int ws = tend - wb;
             int r = tend - 2 * kWave + 1 + lane;
             r = (lane >= kWave - ws && r >= 1 && r <= nA) ? r : 0;
-            out_slot[r] = sh.out_stage[r > 0 ? (r & (kRing - 1)) : kRing];
+            out_slot[r] = sh.out_stage[r > 0 ? ring_slot(r) : kRing];
             if (last >= 1) {
                 __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
                 __hip_atomic_store(out_flag, (uint32_t)(last < nA ? last : nA), __ATOMIC_RELAXED,
@@ -489,7 +528,7 @@ __device__ __forceinline__ void sweep_strip(GroupShared<AT, G> &sh, int w, int g
                 const int ws = tend - wb;
                 const int r = tend - 2 * kWave + 1 + lane;
                 const bool ok = lane >= kWave - ws && r >= 1 && r <= nA;
-                *(ok ? ck_col + r : io.dummy + lane) = out_ring[ok ? (r & (kRing - 1)) : kRing];
+                *(ok ? ck_col + r : io.dummy + lane) = out_ring[ok ? ring_slot(r) : kRing];
             }
         }
     }
@@ -516,8 +555,8 @@ __device__ __forceinline__ void sweep_strip(GroupShared<AT, G> &sh, int w, int g
 // Two global slots suffice: group g+2 writes row r of its boundary only
 // after group g+1 has read row r from the slot both use (it reads a row
 // before its own last wave can produce that row).
-template <typename AT, int G, typename Body>
-__device__ __forceinline__ void claim_groups(GroupShared<AT, G> &sh, uint32_t *ticket, int nStrips, Body &&body)
+template <int G, typename Shared, typename Body>
+__device__ __forceinline__ void claim_groups(Shared &sh, uint32_t *ticket, int nStrips, Body &&body)
 {
     const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
     const int nGroups = (nStrips + G - 1) / G;
@@ -549,9 +588,9 @@ __global__ __launch_bounds__(kWave * G) void wavefront_kernel(const CT *__restri
                                                              const CT *beta_ptr, AT *out, AT *dump, int sub_shift,
                                                              TileIO<AT> io)
 {
-    __shared__ GroupShared<AT, G> sh;
+    __shared__ GroupShared<CT, AT, DIMT, G> sh;
     const CT beta = kShifted<AT> ? beta_ptr[0] : CT(0);
-    claim_groups<AT, G>(sh, ticket, nStrips, [&](int w, int g, int s) {
+    claim_groups<G>(sh, ticket, nStrips, [&](int w, int g, int s) {
         sweep_strip<CT, AT, DIMT, PM, K, G, DUMP, TILE, REC, DIRS>(sh, w, g, s, s * kWave * K, rowsA, rowsB, nA, nB,
                                                                    ca, bnd, flags, err, nStrips, beta, out, dump,
                                                                    sub_shift, io);
@@ -574,9 +613,9 @@ __global__ __launch_bounds__(kWave * G) void wavefront_mixed_kernel(const CT *__
                                                                    int sub_shift)
 {
     static_assert(K2 < K, "the second width is the narrower one");
-    __shared__ GroupShared<AT, G> sh;
+    __shared__ GroupShared<CT, AT, DIMT, G> sh;
     const CT beta = kShifted<AT> ? beta_ptr[0] : CT(0);
-    claim_groups<AT, G>(sh, ticket, nStrips, [&](int w, int g, int s) {
+    claim_groups<G>(sh, ticket, nStrips, [&](int w, int g, int s) {
         if (s < s1)
             sweep_strip<CT, AT, DIMT, PM, K, G, false, false, kRecTwed, false>(
                 sh, w, g, s, s * kWave * K, rowsA, rowsB, nA, nB, ca, bnd, flags, err, nStrips, beta, out,

@@ -316,6 +316,26 @@ def test_handoff_intervals_bitwise(sub, monkeypatch):
             assert v == ref, (sub, k, g, v, ref)
 
 
+@pytest.mark.parametrize("dim,prec", [(1, "f64"), (1, "f32"), (3, "f32"), (8, "f32_acc64"), (8, "f64"), (28, "f64")])
+def test_row_ring_edges_bitwise(dim, prec, monkeypatch):
+    """Rows of A pass through a ring of two 64-row chunks per wave (rows of 28
+    FP64 components and wide strips of large samples come from global memory):
+    row counts around one, two and three chunks and around the hand-over
+    interval, at every strip width and group size, agree to the bit with the
+    per-diagonal sweep, and so does the layout that the sizes pick."""
+    for nA in (1, 31, 33, 63, 64, 65, 127, 128, 129, 193):
+        c = synth.random_pair(nA, 45, nA, 64 * 8 + 3, dim, irregular=True, nu=0.02, lam=0.6, p=2.0)
+        ref = gpu_twed(c.A, c.TA, c.B, c.TB, c.nu, c.lam, c.p, prec, algo="diagonal")
+        say(f"row ring {prec} {dim}-D {nA} rows")
+        assert gpu_twed(c.A, c.TA, c.B, c.TB, c.nu, c.lam, c.p, prec, algo="wavefront") == ref, nA
+        for k in (1, 2, 4, 8) if dim <= 16 else (1, 2):
+            for g in ("1", "4", "8"):
+                monkeypatch.setenv("TWED_WAVEFRONT_GROUP", g)
+                v = gpu_twed(c.A, c.TA, c.B, c.TB, c.nu, c.lam, c.p, prec, algo="wavefront", strip_k=k)
+                assert v == ref, (prec, dim, nA, k, g, v, ref)
+        monkeypatch.delenv("TWED_WAVEFRONT_GROUP")
+
+
 def test_strip_groups_long_pair_vs_oracle(monkeypatch):
     """A pair long enough for many LDS sub-chunks and global windows, in
     groups of 8, against the FP64 oracle (FP32 costs with FP64 accumulators)."""
