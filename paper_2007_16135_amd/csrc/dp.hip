@@ -79,7 +79,6 @@ hipError_t by_config(int rec, Prec prec, const CostParams &cp, int K, int G, Fn 
 hipError_t launch_dp(int rec, Prec prec, const CostParams &cp, int K, const WavefrontArgs &a, const TileArgs &t,
                      hipStream_t st)
 {
-    if (t.dirs) return launch_rec_dirs(rec, prec, cp, K, a, t, st);
     hipError_t e = by_config(rec, prec, cp, K, a.group,
                              [&]<typename CT, typename AT, int DIMT, int PM, int KK, int G, int REC>() -> hipError_t {
                                  TileIO<AT> io{};
@@ -90,7 +89,6 @@ hipError_t launch_dp(int rec, Prec prec, const CostParams &cp, int K, const Wave
                                  io.ckrow = (Pair2<AT> *)t.ckrow;
                                  io.ckcol = (Pair2<AT> *)t.ckcol;
                                  io.dummy = (Pair2<AT> *)t.dummy;
-                                 io.dirs = t.dirs;
                                  io.ck_rows = t.ck_rows;
                                  io.ck_cols = t.ck_cols;
                                  return launch_dp_kg<CT, AT, DIMT, PM, KK, G, REC>(a, io, cp, st);

@@ -48,30 +48,27 @@ struct Sweep {
 
 // The recurrence a sweep runs: kRecTwed, or a sibling (kRecDtw, kRecEdit,
 // kRecIndel; see twed_device.h), whose kernels exist for G in {4, 8} only.
-size_t sweep_scratch(int rec, bool dirs, Prec prec, const CostParams &cp, int K, int G)
+size_t sweep_scratch(int rec, Prec prec, const CostParams &cp, int K, int G)
 {
-    if (dirs) return rec_dirs_scratch_bytes(rec, prec, cp, K, G);
     return rec == kRecTwed ? tile_scratch_bytes(prec, cp, K, G) : dp_scratch_bytes(rec, prec, cp, K, G);
 }
 
-int sweep_workers(int rec, bool dirs, Prec prec, const CostParams &cp, int K, int G)
+int sweep_workers(int rec, Prec prec, const CostParams &cp, int K, int G)
 {
-    if (dirs) return rec_dirs_max_workers(rec, prec, cp, K, G);
     return rec == kRecTwed ? tile_max_workers(prec, cp, K, G) : dp_max_workers(rec, prec, cp, K, G);
 }
 
 // Strip width and group of a sweep of nA x nB cells: the pair sweep's rule
 // (resident_strip_width, groups of four, while the strips fit one wave per
 // SIMD; beyond that the widest strip that leaves three strips for every four
-// SIMDs, in groups of eight).  Move-recording sweeps (dirs) run strips of one
-// column per lane.
-Sweep tile_sweep(int rec, int strip_k, int64_t nA, int64_t nB, Prec prec, const CostParams &cp, bool dirs = false)
+// SIMDs, in groups of eight).
+Sweep tile_sweep(int rec, int strip_k, int64_t nA, int64_t nB, Prec prec, const CostParams &cp)
 {
-    const bool sib = rec != kRecTwed && !dirs;
+    const bool sib = rec != kRecTwed;
     const int64_t n_simds = simds();
-    auto fits = [&](int K, int G) { return sweep_scratch(rec, dirs, prec, cp, K, G) == 0; };
+    auto fits = [&](int K, int G) { return sweep_scratch(rec, prec, cp, K, G) == 0; };
     static const int any[] = {1, 2, 4, 8, 0};
-    const int one[] = {dirs ? 1 : strip_k, 0};
+    const int one[] = {strip_k, 0};
     int G = 4;
     int K = resident_strip_width(one[0] > 0 ? one : any, nA, nB, prec, cp, n_simds, [&](int k) { return fits(k, 4); });
     if (K == 0) {
@@ -91,7 +88,7 @@ Sweep tile_sweep(int rec, int strip_k, int64_t nA, int64_t nB, Prec prec, const 
     // tile sweeps for tuning runs
     if (const char *env = std::getenv("TWED_WAVEFRONT_GROUP")) {
         const int g = std::atoi(env);
-        if (!sib && !dirs && (g == 1 || g == 4 || g == 8) && fits(K, g)) G = g;
+        if (!sib && (g == 1 || g == 4 || g == 8) && fits(K, g)) G = g;
     }
     return Sweep{K, G};
 }
@@ -131,7 +128,7 @@ twed_status run_tile(int rec, Prec prec, const CostParams &cp, Sweep sw, const v
     w.dump = nullptr;
     w.group = sw.G;
     w.sub_shift = kSubShift;
-    const int workers = sweep_workers(rec, t.dirs != nullptr, prec, cp, sw.K, sw.G);
+    const int workers = sweep_workers(rec, prec, cp, sw.K, sw.G);
     if (workers <= 0) return fail(TWED_ERR_DEVICE, "occupancy query failed");
     w.grid = (int)std::min<int64_t>((w.nStrips + sw.G - 1) / sw.G, workers);
     const hipError_t e = rec == kRecTwed ? launch_tile(prec, cp, sw.K, w, t, st)
@@ -153,7 +150,7 @@ size_t row_bytes(Prec prec, int dimt) { return (size_t)row_stride(prec, dimt) * 
 // ---- path layout ---------------------------------------------------------------
 
 struct PathGeometry {
-    Sweep fwd, blk;
+    Sweep fwd;
     int64_t H, Wc, nr, nc;
 };
 
@@ -168,28 +165,87 @@ PathGeometry path_geometry(int rec, const twed_params *prm, int64_t nA, int64_t 
     g.Wc = (std::max(want, W) + W - 1) / W * W;
     g.nr = (nA - 1) / g.H;
     g.nc = (nB - 1) / g.Wc;
-    g.blk = tile_sweep(rec, 0, std::min(g.H, nA), std::min(g.Wc, nB), prec, cp, true);
     return g;
 }
 
 // Edit and indel distances start from finite row 0 / column 0 (i, i).
 bool finite_edges(int rec) { return rec == kRecEdit || rec == kRecIndel; }
 
-// Blocks recomputed with moves at once: the block the walk is in and the
-// three it can leave into (up, left, up-left), each in its own slot.
-constexpr int kPathSlots = 4;
+// Blocks swept again with moves while the walk is in one of them: that block,
+// its neighbours up and to the left, and the blocks that the direction of the
+// last few walks leads to.  A block's sweep takes several times as long as its
+// walk (1.5 ms against 0.2 for 4,096 x 4,096 8-D cells), so it has to start
+// several walks ahead.  Each block has a slot; there are more slots than blocks
+// wanted, so that a new block need not wait for the sweep of one that is no
+// longer wanted.  (With the neighbours only, in four slots, every block was waited
+// for; with squares of blocks the launches held each other up.)
+constexpr int kPathAhead = 8;  // walks
+constexpr int kPathSlots = 24, kPathSlotsMin = 4;
+
+int path_slots(int64_t nr, int64_t nc)
+{
+    return (int)std::clamp<int64_t>((nr + 1) * (nc + 1), kPathSlotsMin, kPathSlots);
+}
+
+struct WantedBlocks {
+    int64_t r[kMaxDirsBlocks], c[kMaxDirsBlocks];
+    int n = 0, near = 0;  // blocks 0 .. near - 1 are the walk's and those it may enter next
+    int limit;
+    bool add(int64_t br, int64_t bc)
+    {
+        if (br < 0 || bc < 0 || n >= limit) return false;
+        for (int i = 0; i < n; ++i)
+            if (r[i] == br && c[i] == bc) return false;
+        r[n] = br;
+        c[n++] = bc;
+        return true;
+    }
+};
+
+// The walk is in block (br, bc), having come `up` blocks up and `left` blocks to
+// the left in its last few walks.
+WantedBlocks wanted_blocks(int64_t br, int64_t bc, int64_t up, int64_t left, int limit)
+{
+    WantedBlocks w;
+    w.limit = limit;
+    w.add(br, bc);
+    w.add(br - 1, bc);
+    w.add(br, bc - 1);
+    w.near = w.n;
+    w.add(br - 1, bc - 1);
+    if (up + left == 0) up = br, left = bc;  // no walk yet: towards (0, 0)
+    if (br == 0) up = 0, left = 1;
+    if (bc == 0) up = 1, left = 0;
+    for (int64_t j = 2; j <= kPathAhead && up + left > 0; ++j) {
+        const int64_t lo = j * up / (up + left), hi = (j * up + up + left - 1) / (up + left);
+        w.add(br - lo, bc - (j - lo));
+        w.add(br - hi, bc - (j - hi));
+        if (j == 2) {
+            w.add(br - 2, bc - 1);
+            w.add(br - 1, bc - 2);
+        }
+    }
+    return w;
+}
+
+// What one block sweep writes: boundary, flags, dummy cells, result and moves.
+struct BlockBuffers {
+    void *bnd, *dummy, *tmp;
+    uint32_t *flags;
+    void *dirs;
+};
 
 struct PathLayout {
     SweepBuffers b;
-    SweepBuffers slot[kPathSlots];  // boundary, flags, dummy and result of one block sweep
-    void *dirs[kPathSlots];
+    BlockBuffers slot[kPathSlots];
+    int64_t zero_words;  // of a slot's flags
     void *ckrow, *ckcol, *row0, *col0;
     int64_t *st;
     size_t total;
 };
 
 PathLayout path_layout(char *base, int rec, const twed_params *prm, int64_t nA, int64_t nB, const PathGeometry &g,
-                       Prec prec)
+                       Prec prec, int slots)
 {
     Carver c{base};
     PathLayout L{};
@@ -201,19 +257,15 @@ PathLayout path_layout(char *base, int rec, const twed_params *prm, int64_t nA, 
     }
     L.ckrow = c.take((size_t)g.nr * (size_t)(nB + 1) * kCell);
     L.ckcol = c.take((size_t)g.nc * (size_t)(nA + 1) * kCell);
-    const int64_t Wb = 64 * (int64_t)g.blk.K;
     const int64_t bh = std::min(g.H, nA), bw = std::min(g.Wc, nB);
-    const int64_t strips = (bw + Wb - 1) / Wb;
-    for (int k = 0; k < kPathSlots; ++k) {
-        SweepBuffers &u = L.slot[k];
-        u.rowsA = L.b.rowsA;
-        u.rowsB = L.b.rowsB;
+    L.zero_words = (bw + 63) / 64 + kTailWords;
+    for (int k = 0; k < slots; ++k) {
+        BlockBuffers &u = L.slot[k];
         u.bnd = c.take((size_t)2 * (size_t)(bh + 1) * kCell);
-        u.zero_words = (bw + 63) / 64 + kTailWords;
-        u.flags = (uint32_t *)c.take((size_t)u.zero_words * 4);
+        u.flags = (uint32_t *)c.take((size_t)L.zero_words * 4);
         u.dummy = c.take(kDummyCells * kCell);
         u.tmp = c.take(8);
-        L.dirs[k] = c.take((size_t)strips * (size_t)(bh + 64) * (size_t)Wb);
+        u.dirs = c.take(dirs_bytes(bh, bw));
     }
     L.total = c.used;
     return L;
@@ -221,28 +273,32 @@ PathLayout path_layout(char *base, int rec, const twed_params *prm, int64_t nA, 
 
 // Side streams and events of the backward pass; the destructor waits for
 // their work (speculative block sweeps may still run) before releasing them.
+// Three streams, taken in turn: with the caller's they fit four hardware queues,
+// and the sweeps started for the walk three blocks earlier have ended.
+constexpr int kPathStreams = 3;
 struct PathStreams {
-    hipStream_t s[kPathSlots] = {};
+    hipStream_t s[kPathStreams] = {};
     hipEvent_t done[kPathSlots] = {};
     hipEvent_t fwd = nullptr;
-    hipError_t create()
+    hipError_t create(int slots)
     {
         hipError_t e = hipEventCreateWithFlags(&fwd, hipEventDisableTiming);
-        for (int k = 0; k < kPathSlots && e == hipSuccess; ++k) {
+        for (int k = 0; k < kPathStreams && e == hipSuccess; ++k)
             e = hipStreamCreateWithFlags(&s[k], hipStreamNonBlocking);
-            if (e == hipSuccess) e = hipEventCreateWithFlags(&done[k], hipEventDisableTiming);
-        }
+        for (int k = 0; k < slots && e == hipSuccess; ++k)
+            e = hipEventCreateWithFlags(&done[k], hipEventDisableTiming);
         return e;
     }
     ~PathStreams()
     {
-        for (int k = 0; k < kPathSlots; ++k) {
+        for (int k = 0; k < kPathStreams; ++k) {
             if (s[k]) {
                 (void)hipStreamSynchronize(s[k]);
                 (void)hipStreamDestroy(s[k]);
             }
-            if (done[k]) (void)hipEventDestroy(done[k]);
         }
+        for (hipEvent_t ev : done)
+            if (ev) (void)hipEventDestroy(ev);
         if (fwd) (void)hipEventDestroy(fwd);
     }
 };
@@ -257,9 +313,13 @@ twed_status path_impl(int rec, const void *A, const void *TA, int64_t nA, const 
     const CostParams cp = cost_params(prm);
     const PathGeometry g = path_geometry(rec, prm, nA, nB, block, prec, cp);
     if (g.H > 0x40000000LL || g.Wc > 0x40000000LL) return fail(TWED_ERR_UNSUPPORTED, "block too large");
-    if ((s = check_workspace(workspace, ws_bytes, path_layout(nullptr, rec, prm, nA, nB, g, prec).total)) != TWED_OK)
+    // (a workspace too small for all slots gets the four it takes at least)
+    int slots = path_slots(g.nr, g.nc);
+    if (path_layout(nullptr, rec, prm, nA, nB, g, prec, slots).total > ws_bytes) slots = kPathSlotsMin;
+    if ((s = check_workspace(workspace, ws_bytes, path_layout(nullptr, rec, prm, nA, nB, g, prec, slots).total)) !=
+        TWED_OK)
         return s;
-    const PathLayout L = path_layout((char *)workspace, rec, prm, nA, nB, g, prec);
+    const PathLayout L = path_layout((char *)workspace, rec, prm, nA, nB, g, prec, slots);
     const SweepBuffers &b = L.b;
     hipError_t e;
 #define TRY(call, what)                                \
@@ -285,28 +345,39 @@ twed_status path_impl(int rec, const void *A, const void *TA, int64_t nA, const 
     s = run_tile(rec, prec, cp, g.fwd, b.rowsA, b.rowsB, nA, nB, b, t, out, st);
     if (s != TWED_OK) return s;
     // Backwards, block by block: sweep the block again recording moves, walk
-    // it.  While the walk runs on the caller's stream, the blocks it can
-    // leave into are swept on side streams, so that the next walk finds its
-    // moves ready: the sweep of a block (latency-bound one-column strips on
-    // a few CUs) then overlaps the walk of the one before.
+    // it.  While the walk runs on the caller's stream, the blocks it and the
+    // next walk can leave into are swept on a side stream, all in one launch,
+    // so that their moves are ready or nearly so when a walk gets there.
     const int64_t cap = nA + nB + 1;
     TRY(launch_walk_init(L.st, nA, nB, st), "walk set-up");
     const size_t rb = row_bytes(prec, dimt_for(prm->dim));
     PathStreams ps;
-    TRY(ps.create(), "stream set-up");
+    TRY(ps.create(slots), "stream set-up");
     TRY(hipEventRecord(ps.fwd, st), "event record");
-    for (int k = 0; k < kPathSlots; ++k) TRY(hipStreamWaitEvent(ps.s[k], ps.fwd, 0), "stream wait");
-    int64_t held[kPathSlots][2];
-    for (int k = 0; k < kPathSlots; ++k) held[k][0] = held[k][1] = -1;
-    // sweeps block (br, bc) with moves into slot k on side stream k
-    auto sweep_block = [&](int k, int64_t br, int64_t bc) -> twed_status {
+    for (int k = 0; k < kPathStreams; ++k) TRY(hipStreamWaitEvent(ps.s[k], ps.fwd, 0), "stream wait");
+    int64_t held[kPathSlots][3];  // block row and column, and the launch that sweeps it
+    for (int k = 0; k < slots; ++k) held[k][0] = held[k][1] = held[k][2] = -1;
+    auto slot_of = [&](int64_t qr, int64_t qc) {
+        for (int k = 0; k < slots; ++k)
+            if (held[k][0] == qr && held[k][1] == qc) return k;
+        return -1;
+    };
+    // block (br, bc) to be swept into slot k
+    auto block_args = [&](int k, int64_t br, int64_t bc) {
         const int64_t r0 = br * g.H, r1 = std::min(r0 + g.H, nA);
         const int64_t c0 = bc * g.Wc, c1 = std::min(c0 + g.Wc, nB);
-        const SweepBuffers &sb = L.slot[k];
-        hipError_t e2 = launch_zero32(sb.flags, sb.zero_words, ps.s[k]);
-        if (e2 != hipSuccess) return fail_hip(e2, "flag reset");
-        TileArgs u{};
+        const BlockBuffers &sb = L.slot[k];
+        DirsArgs u{};
+        u.rowsA = (const char *)b.rowsA + r0 * rb;
+        u.rowsB = (const char *)b.rowsB + c0 * rb;
+        u.nA = r1 - r0;
+        u.nB = c1 - c0;
+        u.bnd = sb.bnd;
+        u.flags = sb.flags;
+        u.ticket = sb.flags + (L.zero_words - kTailWords);
         u.dummy = sb.dummy;
+        u.out = sb.tmp;
+        u.dirs = sb.dirs;
         if (br > 0)
             u.top = (const char *)L.ckrow + ((size_t)(br - 1) * (size_t)(nB + 1) + (size_t)c0) * kCell;
         else if (L.row0)
@@ -315,17 +386,12 @@ twed_status path_impl(int rec, const void *A, const void *TA, int64_t nA, const 
             u.left = (const char *)L.ckcol + ((size_t)(bc - 1) * (size_t)(nA + 1) + (size_t)r0) * kCell;
         else if (L.col0)
             u.left = (const char *)L.col0 + (size_t)r0 * kCell;
-        u.dirs = (uint8_t *)L.dirs[k];
-        const twed_status s2 = run_tile(rec, prec, cp, g.blk, (const char *)b.rowsA + r0 * rb,
-                                        (const char *)b.rowsB + c0 * rb, r1 - r0, c1 - c0, sb, u, sb.tmp, ps.s[k]);
-        if (s2 != TWED_OK) return s2;
-        e2 = hipEventRecord(ps.done[k], ps.s[k]);
-        if (e2 != hipSuccess) return fail_hip(e2, "event record");
-        held[k][0] = br;
-        held[k][1] = bc;
-        return TWED_OK;
+        return u;
     };
     int64_t hst[4] = {0, 0, 0, 0};
+    int64_t launches = 0;
+    constexpr int kTrail = 4;  // walks whose blocks tell the direction
+    int64_t trail[kTrail][2] = {};
     const int64_t max_blocks = g.nr + g.nc + 3;
     for (int64_t it = 0;; ++it) {
         TRY(hipMemcpyAsync(hst, L.st, sizeof(hst), hipMemcpyDeviceToHost, st), "walk state read");
@@ -334,44 +400,62 @@ twed_status path_impl(int rec, const void *A, const void *TA, int64_t nA, const 
         if (hst[3] != 0 || it > max_blocks || hst[0] < 1 || hst[1] < 1)
             return fail(TWED_ERR_DEVICE, "the path could not be followed (non-finite distance or a timed-out sweep)");
         const int64_t br = (hst[0] - 1) / g.H, bc = (hst[1] - 1) / g.Wc;
-        // this block first, then the up, left and up-left neighbours
-        int64_t want[kPathSlots][2];
-        int nw = 0;
-        want[nw][0] = br, want[nw][1] = bc, ++nw;
-        if (br > 0) want[nw][0] = br - 1, want[nw][1] = bc, ++nw;
-        if (bc > 0) want[nw][0] = br, want[nw][1] = bc - 1, ++nw;
-        if (br > 0 && bc > 0) want[nw][0] = br - 1, want[nw][1] = bc - 1, ++nw;
-        auto slot_of = [&](int64_t qr, int64_t qc) {
-            for (int k = 0; k < kPathSlots; ++k)
-                if (held[k][0] == qr && held[k][1] == qc) return k;
-            return -1;
+        auto walk = [&](int kc) -> hipError_t {
+            hipError_t e2 = hipStreamWaitEvent(st, ps.done[kc], 0);
+            if (e2 != hipSuccess) return e2;
+            return launch_walk(L.slot[kc].dirs, br * g.H, bc * g.Wc, std::min(g.H, nA - br * g.H), L.st, path, cap,
+                               finite_edges(rec), st);
         };
-        // slots whose block is not wanted may be overwritten (slot k's
-        // earlier sweep is ordered before the new one on stream k, and every
-        // walk that read it has finished: the caller's stream was synchronised)
+        const bool swept = slot_of(br, bc) >= 0;
+        if (swept) TRY(walk(slot_of(br, bc)), "walk");
+        // A slot whose block is not among those wanted now may be overwritten:
+        // every walk that read it has finished (the caller's stream was
+        // synchronised), and its own sweep is waited for.
+        const int64_t *from = trail[it >= kTrail ? it % kTrail : 0];
+        const int64_t up = it > 0 ? from[0] - br : 0, left = it > 0 ? from[1] - bc : 0;
+        const WantedBlocks want = wanted_blocks(br, bc, up, left, std::min(slots, kMaxDirsBlocks));
+        trail[it % kTrail][0] = br;
+        trail[it % kTrail][1] = bc;
         bool keep[kPathSlots] = {};
-        for (int w = 0; w < nw; ++w) {
-            const int k = slot_of(want[w][0], want[w][1]);
+        int missing = 0;
+        bool near = false;
+        for (int i = 0; i < want.n; ++i) {
+            const int k = slot_of(want.r[i], want.c[i]);
             if (k >= 0) keep[k] = true;
+            else ++missing, near = near || i < want.near;
         }
-        for (int w = 0; w < nw; ++w) {
-            if (slot_of(want[w][0], want[w][1]) >= 0) continue;
-            int k = 0;
-            while (keep[k]) ++k;  // nw <= kPathSlots, so a free slot exists
-            keep[k] = true;
-            if ((s = sweep_block(k, want[w][0], want[w][1])) != TWED_OK) return s;
+        // A walk leaves a few blocks missing; they wait for the next one's, so
+        // that a launch brings more blocks: only as many launches run at a time as
+        // there are side streams.
+        if (near || missing > kPathSlotsMin) {
+            ++launches;
+            hipStream_t side = ps.s[launches % kPathStreams];
+            DirsArgs todo[kMaxDirsBlocks];
+            int at[kMaxDirsBlocks], nt = 0;
+            for (int i = 0; i < want.n; ++i) {
+                if (slot_of(want.r[i], want.c[i]) >= 0) continue;
+                // of the slots that hold no wanted block (there is one: no more
+                // blocks are wanted than there are slots) the one swept longest ago
+                int k = -1;
+                for (int f = 0; f < slots; ++f)
+                    if (!keep[f] && (k < 0 || held[f][2] < held[k][2])) k = f;
+                keep[k] = true;
+                if (held[k][0] >= 0) TRY(hipStreamWaitEvent(side, ps.done[k], 0), "stream wait");
+                held[k][0] = want.r[i];
+                held[k][1] = want.c[i];
+                held[k][2] = launches;
+                todo[nt] = block_args(k, want.r[i], want.c[i]);
+                at[nt++] = k;
+            }
+            TRY(launch_zero_flags(todo, nt, L.zero_words, side), "flag reset");
+            TRY(launch_dirs(rec, prec, cp, todo, nt, side), "block sweep");
+            for (int i = 0; i < nt; ++i) TRY(hipEventRecord(ps.done[at[i]], side), "event record");
         }
-        const int kc = slot_of(br, bc);
-        const int64_t r0 = br * g.H, r1 = std::min(r0 + g.H, nA);
-        const int64_t c0 = bc * g.Wc, c1 = std::min(c0 + g.Wc, nB);
-        TRY(hipStreamWaitEvent(st, ps.done[kc], 0), "stream wait");
-        TRY(launch_walk((const uint8_t *)L.dirs[kc], r0, c0, r1 - r0, c1 - c0, g.blk.K, (r1 - r0) + 64, L.st, path,
-                        cap, finite_edges(rec), st),
-            "walk");
+        if (!swept) TRY(walk(slot_of(br, bc)), "walk");
     }
     // later work on the caller's stream (and its reuse of the workspace)
     // stays behind speculative sweeps still running
-    for (int k = 0; k < kPathSlots; ++k)
+    for (int k = 0; k < slots; ++k)
         if (held[k][0] >= 0) TRY(hipStreamWaitEvent(st, ps.done[k], 0), "stream wait");
     TRY(launch_order(L.st, path, path_len, cap, st), "path order");
     // the path and its length are complete when the call returns
@@ -466,7 +550,7 @@ size_t twed_pair_path_workspace_size(int64_t nA, int64_t nB, const twed_params *
     if (check_params(prm) != TWED_OK || !tile_prec(prm, &prec)) return 0;
     const CostParams cp = cost_params(prm);
     const PathGeometry g = path_geometry(kRecTwed, prm, nA, nB, block, prec, cp);
-    return path_layout(nullptr, kRecTwed, prm, nA, nB, g, prec).total;
+    return path_layout(nullptr, kRecTwed, prm, nA, nB, g, prec, path_slots(g.nr, g.nc)).total;
 }
 
 twed_status twed_pair_path(const void *A, const void *TA, int64_t nA, const void *B, const void *TB, int64_t nB,
@@ -540,7 +624,7 @@ size_t twed_dp_path_workspace_size(int32_t kind, int64_t nA, int64_t nB, const t
     const int rec = rec_of(kind);
     const CostParams cp = cost_params(prm);
     const PathGeometry g = path_geometry(rec, prm, nA, nB, block, prec, cp);
-    return path_layout(nullptr, rec, prm, nA, nB, g, prec).total;
+    return path_layout(nullptr, rec, prm, nA, nB, g, prec, path_slots(g.nr, g.nc)).total;
 }
 
 twed_status twed_dp_path(int32_t kind, const void *A, int64_t nA, const void *B, int64_t nB, const twed_params *prm,

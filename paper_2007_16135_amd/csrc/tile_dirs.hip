@@ -1,47 +1,72 @@
-// tile_dirs.hip -- the tile sweep that also records the move into every cell
-// (one byte per cell, for reading an alignment path back).  Kept apart from
+// tile_dirs.hip -- sweeps of blocks that also record the move into every cell
+// (two bits per cell, for reading an alignment path back).  Kept apart from
 // tile.hip: the recording code needs registers that the plain tile kernels
-// then do not pay for.  Strips of one column per lane only (the blocks this
-// sweeps are a few thousand columns wide).
+// then do not pay for.  Strips of one column per lane in groups of four.
 #include "wavefront_impl.h"
 
+#include <algorithm>
 #include <type_traits>
 
 namespace twed {
 
 namespace {
 
-template <typename CT, typename AT, int DIMT, int PM, int G, int REC>
-hipError_t launch_g(const WavefrontArgs &a, const TileIO<AT> &io, const CostParams &cp, hipStream_t st)
+constexpr int kDirsGroup = 4;
+
+template <typename CT, typename AT>
+struct DirsBlock {
+    const CT *rowsA, *rowsB;
+    const Pair2<AT> *top, *left;
+    Pair2<AT> *bnd, *dummy;
+    uint32_t *flags, *ticket;
+    AT *out;
+    uint64_t *dirs;
+    int nA, nB;
+};
+
+template <typename CT, typename AT>
+struct DirsBlocks {
+    DirsBlock<CT, AT> b[kMaxDirsBlocks];
+};
+
+// Workgroups (., y) sweep block y, each block with its own ticket, flags and
+// boundary slots.  One block keeps 16 of 256 compute units busy (4,096 columns)
+// and takes what its chain of diagonals takes, so the blocks a path may cross
+// next run in the same launch beside it: as launches of their own on four
+// streams, four ran at once at most (one hardware queue each), the walk among
+// them.
+template <typename CT, typename AT, int DIMT, int PM, int REC>
+__global__ __launch_bounds__(kWave * kDirsGroup) void dirs_kernel(DirsBlocks<CT, AT> blocks, CostArgs<CT> ca,
+                                                                 int sub_shift)
 {
-    hipLaunchKernelGGL((wavefront_kernel<CT, AT, DIMT, PM, 1, G, false, true, REC, true>), dim3(a.grid),
-                       dim3(kWave * G), 0, st, (const CT *)a.rowsA, (const CT *)a.rowsB, (int)a.nA, (int)a.nB,
-                       CostArgs<CT>::make(cp), (Pair2<AT> *)a.bnd, a.flags, a.ticket, a.ticket + 1, (int)a.nStrips,
-                       (const CT *)a.beta, (AT *)a.out, nullptr, a.sub_shift, io);
-    return hipGetLastError();
+    __shared__ GroupShared<CT, AT, DIMT, kDirsGroup> sh;
+    const DirsBlock<CT, AT> &d = blocks.b[blockIdx.y];
+    const int nStrips = (d.nB + kWave - 1) / kWave;
+    TileIO<AT> io{};
+    io.top = d.top;
+    io.left = d.left;
+    io.dummy = d.dummy;
+    io.dirs = d.dirs;
+    claim_groups<kDirsGroup>(sh, d.ticket, nStrips, [&](int w, int g, int s) {
+        sweep_strip<CT, AT, DIMT, PM, 1, kDirsGroup, false, true, REC, true>(
+            sh, w, g, s, s * kWave, d.rowsA, d.rowsB, d.nA, d.nB, ca, d.bnd, d.flags, d.ticket + 1, nStrips, CT(0),
+            d.out, nullptr, sub_shift, io);
+    });
 }
 
 template <int REC, int DIMT>
 constexpr bool kRecDim = REC == kRecTwed || REC == kRecDtw || DIMT == 1;
 
-// fn.template operator()<CT, AT, DIMT, PM, G, REC>() for a compiled
-// configuration (K = 1; G = 1, 4 or 8; FP64 accumulators).
+// fn.template operator()<CT, AT, DIMT, PM, REC>() for a compiled configuration
+// (FP64 accumulators).
 template <typename Fn>
-hipError_t by_config(int rec, Prec prec, const CostParams &cp, int G, Fn &&fn)
+hipError_t by_config(int rec, Prec prec, const CostParams &cp, Fn &&fn)
 {
     if (prec != kF64 && prec != kF32Acc64) return hipErrorInvalidValue;
     auto with_rec = [&]<int REC>() -> hipError_t {
         return by_prec(prec, cp.dimt, cp.pm, [&]<typename CT, typename AT, int DIMT, int PM>() -> hipError_t {
-            if constexpr (!std::is_same_v<AT, double> || !kRecDim<REC, DIMT>) {
-                return hipErrorInvalidValue;
-            } else {
-                switch (G) {
-                case 1: return fn.template operator()<CT, AT, DIMT, PM, 1, REC>();
-                case 4: return fn.template operator()<CT, AT, DIMT, PM, 4, REC>();
-                case 8: return fn.template operator()<CT, AT, DIMT, PM, 8, REC>();
-                default: return hipErrorInvalidValue;
-                }
-            }
+            if constexpr (!std::is_same_v<AT, double> || !kRecDim<REC, DIMT>) return hipErrorInvalidValue;
+            else return fn.template operator()<CT, AT, DIMT, PM, REC>();
         });
     };
     switch (rec) {
@@ -55,58 +80,29 @@ hipError_t by_config(int rec, Prec prec, const CostParams &cp, int G, Fn &&fn)
 
 }  // namespace
 
-hipError_t launch_rec_dirs(int rec, Prec prec, const CostParams &cp, int K, const WavefrontArgs &a, const TileArgs &t,
-                           hipStream_t st)
+hipError_t launch_dirs(int rec, Prec prec, const CostParams &cp, const DirsArgs *blocks, int n, hipStream_t st)
 {
-    if (K != 1 || !t.dirs) return hipErrorInvalidValue;
-    hipError_t e = by_config(rec, prec, cp, a.group, [&]<typename CT, typename AT, int DIMT, int PM, int G, int REC>() {
-        TileIO<AT> io{};
-        io.top = (const Pair2<AT> *)t.top;
-        io.left = (const Pair2<AT> *)t.left;
-        io.bottom = (Pair2<AT> *)t.bottom;
-        io.right = (Pair2<AT> *)t.right;
-        io.ckrow = (Pair2<AT> *)t.ckrow;
-        io.ckcol = (Pair2<AT> *)t.ckcol;
-        io.dummy = (Pair2<AT> *)t.dummy;
-        io.dirs = t.dirs;
-        io.ck_rows = t.ck_rows;
-        io.ck_cols = t.ck_cols;
-        return launch_g<CT, AT, DIMT, PM, G, REC>(a, io, cp, st);
+    if (n <= 0) return hipSuccess;
+    if (n > kMaxDirsBlocks) return hipErrorInvalidValue;
+    return by_config(rec, prec, cp, [&]<typename CT, typename AT, int DIMT, int PM, int REC>() -> hipError_t {
+        DirsBlocks<CT, AT> g{};
+        int64_t groups = 0;
+        for (int i = 0; i < n; ++i) {
+            const DirsArgs &a = blocks[i];
+            const int64_t strips = (a.nB + kWave - 1) / kWave;
+            groups = std::max(groups, (strips + kDirsGroup - 1) / kDirsGroup);
+            g.b[i] = DirsBlock<CT, AT>{(const CT *)a.rowsA,     (const CT *)a.rowsB, (const Pair2<AT> *)a.top,
+                                       (const Pair2<AT> *)a.left, (Pair2<AT> *)a.bnd,  (Pair2<AT> *)a.dummy,
+                                       a.flags,                 a.ticket,            (AT *)a.out,
+                                       (uint64_t *)a.dirs,      (int)a.nA,           (int)a.nB};
+        }
+        // (workgroups claim groups until none is left: a grid smaller than the
+        // groups of one very wide block is enough)
+        const int grid = (int)std::min<int64_t>(groups, 1024);
+        hipLaunchKernelGGL((dirs_kernel<CT, AT, DIMT, PM, REC>), dim3(grid, n), dim3(kWave * kDirsGroup), 0, st, g,
+                           CostArgs<CT>::make(cp), kSubShift);
+        return hipGetLastError();
     });
-    if (e != hipSuccess) return e;
-    return launch_tile_edges(a.nA, a.nB, t, st);
-}
-
-hipError_t launch_tile_dirs(Prec prec, const CostParams &cp, int K, const WavefrontArgs &a, const TileArgs &t,
-                            hipStream_t st)
-{
-    return launch_rec_dirs(kRecTwed, prec, cp, K, a, t, st);
-}
-
-size_t rec_dirs_scratch_bytes(int rec, Prec prec, const CostParams &cp, int K, int G)
-{
-    size_t bytes = (size_t)-1;
-    if (K != 1) return bytes;
-    (void)by_config(rec, prec, cp, G, [&]<typename CT, typename AT, int DIMT, int PM, int GG, int REC>() {
-        bytes = scratch_kg<CT, AT, DIMT, PM, 1, GG, true, REC, true>();
-        return hipSuccess;
-    });
-    return bytes;
-}
-
-int rec_dirs_max_workers(int rec, Prec prec, const CostParams &cp, int K, int G)
-{
-    int per_cu = 0;
-    if (K != 1) return 0;
-    (void)by_config(rec, prec, cp, G, [&]<typename CT, typename AT, int DIMT, int PM, int GG, int REC>() {
-        per_cu = occupancy_kg<CT, AT, DIMT, PM, 1, GG, true, REC, true>();
-        return hipSuccess;
-    });
-    if (per_cu <= 0) return 0;
-    int dev = 0, cus = 0;
-    if (hipGetDevice(&dev) != hipSuccess) return 0;
-    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
-    return per_cu * cus;
 }
 
 }  // namespace twed

@@ -109,7 +109,6 @@ struct TileArgs {
     void *ckrow;        // rows ck_rows, 2*ck_rows, ... < nA, nB + 1 cells each
     void *ckcol;        // columns ck_cols, 2*ck_cols, ... < nB, nA + 1 cells each
     void *dummy;        // 512 cells of scratch
-    uint8_t *dirs;      // moves, nStrips * (nA + 64) * 64 * K bytes (recording kernels, K = 1)
     int ck_rows;        // >= 64
     int ck_cols;        // a multiple of the strip width 64*K
 };
@@ -128,25 +127,37 @@ hipError_t launch_tile_edges(int64_t nA, int64_t nB, const TileArgs &t, hipStrea
 // (size_t)-1 / 0.
 hipError_t launch_dp(int rec, Prec prec, const CostParams &cp, int K, const WavefrontArgs &a, const TileArgs &t,
                      hipStream_t st);
-// Tile sweeps that record moves (t.dirs set; tile_dirs.hip): any recurrence,
-// K = 1 only, G = 1, 4 or 8.  launch_tile / launch_dp with t.dirs set call
-// these.
-hipError_t launch_tile_dirs(Prec prec, const CostParams &cp, int K, const WavefrontArgs &a, const TileArgs &t,
-                            hipStream_t st);
-hipError_t launch_rec_dirs(int rec, Prec prec, const CostParams &cp, int K, const WavefrontArgs &a, const TileArgs &t,
-                           hipStream_t st);
-size_t rec_dirs_scratch_bytes(int rec, Prec prec, const CostParams &cp, int K, int G);
-int rec_dirs_max_workers(int rec, Prec prec, const CostParams &cp, int K, int G);
 size_t dp_scratch_bytes(int rec, Prec prec, const CostParams &cp, int K, int G);
 int dp_max_workers(int rec, Prec prec, const CostParams &cp, int K, int G);
 
+// Sweeps that record the move into every cell (tile_dirs.hip), any recurrence,
+// FP64 accumulators: one block of nA x nB cells with its row 0 / column 0 cells
+// in top / left (null: pad), its rows at rowsA / rowsB, and what it writes.
+struct DirsArgs {
+    const void *rowsA, *rowsB, *top, *left;
+    void *bnd, *dummy, *out;  // two boundary slots of nA + 1 cells, 512 cells, one cell value
+    uint32_t *flags, *ticket; // zeroed; ticket[1] is the wait error word
+    void *dirs;               // moves, dirs_bytes(nA, nB), 16-byte aligned
+    int64_t nA, nB;
+};
+constexpr int kMaxDirsBlocks = 20;
+// Strips of 64 columns, each ceil((nA + 64) / 32) pieces of 32 steps: 64 bits
+// per lane in each (see TileIO).
+inline size_t dirs_bytes(int64_t nA, int64_t nB)
+{
+    return (size_t)((nB + 63) / 64) * (size_t)((nA + 64 + 31) / 32) * 512;
+}
+// n <= kMaxDirsBlocks blocks in one launch.
+hipError_t launch_dirs(int rec, Prec prec, const CostParams &cp, const DirsArgs *blocks, int n, hipStream_t st);
+// Zeroes the first `words` words of every block's flags.
+hipError_t launch_zero_flags(const DirsArgs *blocks, int n, int64_t words, hipStream_t s);
+
 // Path read-back (path.hip).  st holds {r, c, cells written, status}.
 hipError_t launch_walk_init(int64_t *st, int64_t nA, int64_t nB, hipStream_t s);
-// Follows the moves of the block (nAt x nBt cells) whose row 0 / column 0
-// are global row r0 / column c0 (dirs in the tile sweep's order with strip
-// width 64*K and T = nAt + 64 steps per strip) until the walk leaves it.
-hipError_t launch_walk(const uint8_t *dirs, int64_t r0, int64_t c0, int64_t nAt, int64_t nBt, int K, int64_t T,
-                       int64_t *st, int64_t *rev, int64_t cap, bool free_edges, hipStream_t s);
+// Follows the moves of the block of nAt rows whose row 0 / column 0 are global
+// row r0 / column c0 (dirs as launch_dirs records them) until the walk leaves it.
+hipError_t launch_walk(const void *dirs, int64_t r0, int64_t c0, int64_t nAt, int64_t *st, int64_t *rev, int64_t cap,
+                       bool free_edges, hipStream_t s);
 // n + 1 (DP, X) cells (i, i), i = 0..n: the boundary of edit / indel distances.
 hipError_t launch_index_cells(void *cells, int64_t n, hipStream_t s);
 // out[0] = (nA + nB - out[0]) / 2: the LCS length from the indel distance.

@@ -36,6 +36,8 @@ constexpr int kRing = 128;
 __host__ __device__ constexpr int ring_slot(int r) { return (r - 1) & (kRing - 1); }
 // Most steps between two updates of the boundary addresses.
 constexpr int kMaxUnroll = 4;
+// No row of any lane (rows run from -63).
+constexpr int kNoRow = -0x40000000;
 
 // Rows of A reach the lanes through LDS: every 64 steps lane l of a wave loads
 // row t + l and writes it to the wave's ring, and at step t lane l reads row
@@ -97,9 +99,10 @@ __device__ __forceinline__ void wait_progress(const uint32_t *p, uint32_t need, 
 //   ckcol   receives columns ck_cols, 2*ck_cols, ... left of nB (nA + 1
 //           cells each; row 0 is left to the host); ck_cols is a multiple
 //           of the strip width
-//   dirs    (DIRS kernels) one byte per cell, the move into it (0 match,
-//           1 deletion in A from the cell above, 2 deletion in B from the
-//           cell on the left), in sweep order: strip s, step t, lane, column
+//   dirs    (DIRS kernels, K = 1) the move into every cell, in sweep order:
+//           strip s, 32 steps, lane, 64 bits of two per step (1 the match, 2 the
+//           deletion in B from the cell on the left, 0 the deletion in A from
+//           the cell above); ceil((nA + 64) / 32) * 64 words per strip
 //   dummy   64*K cells that lanes without a cell to store write instead
 template <typename AT>
 struct TileIO {
@@ -110,19 +113,10 @@ struct TileIO {
     Pair2<AT> *ckrow;
     Pair2<AT> *ckcol;
     Pair2<AT> *dummy;
-    uint8_t *dirs;
+    uint64_t *dirs;
     int ck_rows;
     int ck_cols;
 };
-
-template <int K>
-__device__ __forceinline__ void store_dirs(uint8_t *p, uint64_t code)
-{
-    if constexpr (K == 8) *reinterpret_cast<uint64_t *>(p) = code;
-    else if constexpr (K == 4) *reinterpret_cast<uint32_t *>(p) = (uint32_t)code;
-    else if constexpr (K == 2) *reinterpret_cast<uint16_t *>(p) = (uint16_t)code;
-    else *p = (uint8_t)code;
-}
 
 // Strip widths compiled for a sample dimension: beyond 16 components a lane
 // holds at most two columns (wider strips would not fit the register file).
@@ -162,7 +156,8 @@ __device__ __forceinline__ void sweep_strip(GroupShared<CT, AT, DIMT, G> &sh, in
 {
     static_assert(REC == kRecTwed || TILE, "sibling recurrences run as tiles");
     static_assert(!DIRS || TILE, "moves are recorded by tile sweeps");
-    const int kSub = 1 << sub_shift;
+    static_assert(!DIRS || K == 1, "moves are packed by lane");
+    const int kSub = DIRS ? 32 : 1 << sub_shift;
     constexpr int S = Row<CT, DIMT>::kStride;
     constexpr int W = kWave * K;
     const int lane = threadIdx.x & (kWave - 1);
@@ -218,6 +213,30 @@ __device__ __forceinline__ void sweep_strip(GroupShared<CT, AT, DIMT, G> &sh, in
         if (io.ckcol != nullptr && has_out && (cbase + W) % io.ck_cols == 0)
             ck_col = io.ckcol + (size_t)((cbase + W) / io.ck_cols - 1) * (size_t)(nA + 1);
     }
+
+    // A tile's top-row cells wait in registers for the step at which the lane
+    // sits on row 0, and the cells of a row that is stored (the last, or a
+    // checkpoint) until every lane has swept it.  A strip follows the one before
+    // it by some 110 steps, so what the 64 steps around such a row cost more than
+    // others is paid again in every strip along the front: dummy stores by the
+    // other lanes, a branch, a load or the wait for stores at the next hand-over.
+    // (Forward sweep of a path of 100,000 8-D samples: 53.4 ms with dummy stores,
+    // 38.8 with branches, now 34.)  Wide strips have no registers to spare.
+    constexpr bool kCellsKept = TILE && K <= 2;
+    Pair2<AT> tops[kCellsKept ? K : 1], kept[kCellsKept ? K : 1];
+    if constexpr (kCellsKept) {
+#pragma unroll
+        for (int j = 0; j < K; ++j) {
+            tops[j] = io.top != nullptr ? io.top[c0 + j <= nB ? c0 + j : nB] : Pair2<AT>{INF, INF};
+            kept[j] = Pair2<AT>{INF, INF};
+        }
+    }
+    // the first checkpoint row not yet passed by every lane, and where it goes
+    // (rows at least 128 apart, so that one is kept at a time)
+    int ck_next = io.ck_rows;
+    Pair2<AT> *ck_row = io.ckrow;
+    const bool rows_kept =
+        kCellsKept && !DIRS && (io.ckrow == nullptr || (io.bottom == nullptr && io.ck_rows >= 2 * kWave));
 
     const int T = nA + kWave;  // lane 63 reaches row nA at step nA + 63
     // The last strip stops once lane lstar has swept row nA (its lanes past
@@ -353,12 +372,41 @@ __device__ __forceinline__ void sweep_strip(GroupShared<CT, AT, DIMT, G> &sh, in
         const Pair2<AT> *in_at = in_src + (t0 & in_mask);
         Pair2<AT> *out_at = has_out && lane == kWave - 1 ? out_ring + ring_slot(t0 - (kWave - 1)) : &sh.dummy[lane];
         const int out_step = has_out && lane == kWave - 1 ? 1 : 0;
+        // Tiles: which rows of interest do lanes reach in this sub-chunk: row 0
+        // (top row), nA (bottom row), a checkpoint row?  Or is this the strip
+        // that hands out column nB at every step?
+        bool sp_top = false, sp_rows = false, sp_right = false;
+        int ck_lo = kNoRow, ck_hi = kNoRow;  // checkpoint rows
+        int keep = kNoRow;                   // the row whose cells are kept
+        int top_step = kNoRow;               // the step at which this lane is on row 0
+        if constexpr (TILE) {
+            const int r_lo = t0 - (kWave - 1), r_hi = t0 + steps - 1;  // rows the lanes touch
+            sp_top = io.top != nullptr && t0 < kWave;
+            if (sp_top) top_step = lane;
+            if constexpr (!DIRS) {
+                sp_right = io.right != nullptr && result_strip;
+                if (io.ckrow != nullptr) {
+                    // at most two checkpoint rows (ck_rows >= 64) are among the
+                    // at most 95 rows of the range
+                    if (ck_next < r_lo) {
+                        ck_next += io.ck_rows;
+                        ck_row += nB + 1;
+                    }
+                    if (ck_next <= r_hi && ck_next < nA) ck_lo = ck_next;
+                    if (ck_next + io.ck_rows <= r_hi && ck_next + io.ck_rows < nA) ck_hi = ck_next + io.ck_rows;
+                }
+                const bool last_row = io.bottom != nullptr && nA <= r_hi;
+                if (rows_kept) keep = last_row ? nA : ck_lo;
+                sp_rows = last_row || ck_lo != kNoRow;
+            }
+        }
+        uint32_t d_lo = 0, d_hi = 0;  // this sub-chunk's moves, the last step in the highest bits
         // One step: sweep row t - lane with `use`, read row t + 1 - lane into
         // `fill`; OFF is the step's place in its unrolled run.  Steps alternate
         // the row buffers, so the row read ahead never has to be copied.  SP
-        // (tile sweeps): this sub-chunk holds a step where top-row cells enter
-        // or boundary cells leave; the other sub-chunks run without testing for
-        // them at every step.
+        // (tile sweeps): lanes meet a row of interest in this sub-chunk; the
+        // other sub-chunks run without testing for them at every step.  Where
+        // cells are kept, the step only selects by lane.
         auto step = [&]<bool SP, int OFF>(int i, Row<CT, DIMT> &use, Row<CT, DIMT> &fill) {
             static_assert(OFF < kMaxUnroll, "sh.dummy has room for this many");
             const int t = t0 + i;
@@ -370,13 +418,14 @@ __device__ __forceinline__ void sweep_strip(GroupShared<CT, AT, DIMT, G> &sh, in
             AT left = sh_l, xl;
             if constexpr (TILE) {
                 if constexpr (DIRS) {
-                    uint64_t code;
+                    uint32_t code;
                     if constexpr (REC == kRecTwed)
-                        code = lane_row_dirs<CT, AT, DIMT, PM, K>(L, use, left, sh_xo, xl, ca.nu, ca.p, ca.invp);
+                        code = (uint32_t)lane_row_dirs<CT, AT, DIMT, PM, K>(L, use, left, sh_xo, xl, ca.nu, ca.p, ca.invp);
                     else
-                        code = lane_row_sibling<CT, AT, DIMT, PM, K, REC, true>(L, use, left, sh_xo, xl, ca.p,
+                        code = (uint32_t)lane_row_sibling<CT, AT, DIMT, PM, K, REC, true>(L, use, left, sh_xo, xl, ca.p,
                                                                                 ca.invp);
-                    store_dirs<K>(io.dirs + (((size_t)s * (size_t)T + (size_t)t) * kWave + lane) * K, code);
+                    d_lo = __builtin_amdgcn_alignbit(d_hi, d_lo, 2);
+                    d_hi = __builtin_amdgcn_alignbit(code == 0 ? 1u : code & 2u, d_hi, 2);
                 } else {
                     if constexpr (REC == kRecTwed)
                         lane_row<CT, AT, DIMT, PM, K>(L, use, left, sh_xo, xl, ca.nu, ca.p, ca.invp, beta);
@@ -386,40 +435,45 @@ __device__ __forceinline__ void sweep_strip(GroupShared<CT, AT, DIMT, G> &sh, in
                 }
               if constexpr (SP) {
                 // the lane sits on row 0: its top-row cells replace the pad state
-                if (io.top != nullptr && t < kWave) {
-                    const bool own = t == lane;
+                if (kCellsKept || sp_top) {
+                    const bool own = t == top_step;
 #pragma unroll
                     for (int j = 0; j < K; ++j) {
-                        const Pair2<AT> v = io.top[c0 + j <= nB ? c0 + j : nB];
+                        Pair2<AT> v;
+                        if constexpr (kCellsKept) v = tops[j];
+                        else v = io.top[c0 + j <= nB ? c0 + j : nB];
                         L.up[j] = own ? v.dp : L.up[j];
                         L.xp[j] = own ? v.x : L.xp[j];
                     }
                     left = own ? L.up[K - 1] : left;
                     xl = own ? L.xp[K - 1] : xl;
                 }
-                // rows stored at this step (every lane stores; lanes without
-                // such a row write the dummy cells)
-                const bool cap_last = io.bottom != nullptr && nA >= t - (kWave - 1) && nA <= t;
-                int kr = 0;
-                if (io.ckrow != nullptr) {
-                    const int m = t / io.ck_rows * io.ck_rows;
-                    kr = (m >= io.ck_rows && m >= t - (kWave - 1) && m < nA) ? m : 0;
-                }
-                if (cap_last || kr > 0) {
-                    const int r = t - lane;
-                    const bool own_last = cap_last && r == nA;
-                    const bool own = own_last || (kr > 0 && r == kr);
-                    Pair2<AT> *base = own_last ? io.bottom
-                                               : io.ckrow + (size_t)(kr > 0 ? kr / io.ck_rows - 1 : 0) *
-                                                                (size_t)(nB + 1);
+                if constexpr (kCellsKept && !DIRS) {
+                    const bool own = t - lane == keep;
 #pragma unroll
                     for (int j = 0; j < K; ++j) {
-                        Pair2<AT> *dst = (own && c0 + j <= nB) ? base + (c0 + j) : io.dummy + lane * K + j;
-                        *dst = Pair2<AT>{L.up[j], L.xp[j]};
+                        kept[j].dp = own ? L.up[j] : kept[j].dp;
+                        kept[j].x = own ? L.xp[j] : kept[j].x;
                     }
                 }
+                // (every lane stores; lanes without a cell of the row write the
+                // dummy cells)
+                auto store_row = [&](int r, Pair2<AT> *row) {
+                    if (r <= t && r >= t - (kWave - 1)) {
+#pragma unroll
+                        for (int j = 0; j < K; ++j) {
+                            Pair2<AT> *dst = t - lane == r && c0 + j <= nB ? row + (c0 + j) : io.dummy + lane * K + j;
+                            *dst = Pair2<AT>{L.up[j], L.xp[j]};
+                        }
+                    }
+                };
+                if (!DIRS && !rows_kept) {
+                    if (io.bottom != nullptr) store_row(nA, io.bottom);
+                    if (ck_lo != kNoRow) store_row(ck_lo, ck_row);
+                    if (ck_hi != kNoRow) store_row(ck_hi, ck_row + (nB + 1));
+                }
                 // column nB (lane lstar, column jstar of the last strip)
-                if (io.right != nullptr && result_strip && t - lstar >= 1 && t - lstar <= nA) {
+                if (!DIRS && sp_right && t - lstar >= 1 && t - lstar <= nA) {
                     AT dp = L.up[0], x = L.xp[0];
 #pragma unroll
                     for (int j = 1; j < K; ++j) {
@@ -475,20 +529,7 @@ __device__ __forceinline__ void sweep_strip(GroupShared<CT, AT, DIMT, G> &sh, in
             }
         };
         if constexpr (TILE) {
-            // does a lane reach row 0 (top row), nA (bottom row) or a
-            // checkpoint row in this sub-chunk, or is this the strip that
-            // hands out column nB at every step?
-            const int r_lo = t0 - (kWave - 1), r_hi = t0 + steps - 1;  // rows the lanes touch
-            bool sp = (io.top != nullptr && t0 < kWave) || (io.right != nullptr && result_strip) ||
-                      (io.bottom != nullptr && nA >= r_lo && nA <= r_hi);
-            if (io.ckrow != nullptr) {
-                // the two multiples of ck_rows (>= 64) at or below r_hi cover
-                // the at most 95 rows of the range
-                const int m = r_hi / io.ck_rows * io.ck_rows;
-                for (int q = m; q >= m - io.ck_rows; q -= io.ck_rows)
-                    sp = sp || (q >= io.ck_rows && q >= r_lo && q < nA);
-            }
-            if (sp) run.template operator()<true>();
+            if (sp_top || sp_rows || sp_right) run.template operator()<true>();
             else run.template operator()<false>();
         } else {
             run.template operator()<false>();
@@ -522,7 +563,17 @@ __device__ __forceinline__ void sweep_strip(GroupShared<CT, AT, DIMT, G> &sh, in
                                    __HIP_MEMORY_SCOPE_AGENT);
             }
         }
+        if constexpr (DIRS)  // (behind the hand-over, which waits for outstanding stores)
+            io.dirs[((size_t)s * (size_t)((T + 31) / 32) + (size_t)(t0 / 32)) * kWave + lane] =
+                ((uint64_t)d_hi << 32 | d_lo) >> (2 * (32 - steps));
         if constexpr (TILE) {
+            if (keep != kNoRow && (tend - 1 >= keep + kWave - 1 || tend >= T_run)) {
+                // every lane (with a column of the block) has swept the row
+                Pair2<AT> *to = keep == nA ? io.bottom : ck_row;
+#pragma unroll
+                for (int j = 0; j < (kCellsKept ? K : 0); ++j)
+                    *(c0 + j <= nB ? to + (c0 + j) : io.dummy + lane * K + j) = kept[j];
+            }
             // a checkpoint column at this strip's right edge, window by window
             if (ck_col != nullptr && (q == (kWindow >> sub_shift) - 1 || tend >= T)) {
                 const int ws = tend - wb;

@@ -173,6 +173,42 @@ def test_path_ties_follow_the_rule():
         assert np.array_equal(path.cpu().numpy(), want)
 
 
+@pytest.mark.parametrize("nA,nB", [(31, 33), (32, 64), (33, 65), (64, 32), (129, 63), (1500, 40), (40, 1500),
+                                   (700, 650), (1000, 960)])
+def test_path_windows_and_blocks_follow_the_rule(nA, nB):
+    """Integer data (every sum exact), the oracle's path cell for cell: rows and
+    columns around the walk's windows of 32 rows, its 320 steps per strip and
+    its 64-column strips, runs of deletions longer than both, blocks whose
+    checkpoint rows are stored at once (64) and kept (192), more blocks than
+    slots, and a workspace one byte short of all slots (four are used)."""
+    import ctypes
+    rng = np.random.default_rng(nA * 7 + nB)
+    A, B = rng.integers(-3, 4, nA).astype(np.float64), rng.integers(-3, 4, nB).astype(np.float64)
+    TA, TB = np.cumsum(rng.integers(0, 3, nA)).astype(np.float64), np.cumsum(rng.integers(0, 3, nB)).astype(np.float64)
+    d = [torch.as_tensor(a, device="cuda") for a in (A.reshape(-1, 1), TA, B.reshape(-1, 1), TB)]
+    L = tw.load_library()
+    for nu, lam in ((0.0, 1.0), (1.0, 0.0)):
+        want = oracle.get().path(A, TA, B, TB, nu, lam, 1.0)
+        dist = oracle.get().twed(A, TA, B, TB, nu, lam, 1.0)
+        prm = ctypes.byref(tw.make_params(nu, lam, 1.0, 1, "f64"))
+        for block in (0, 64, 192):
+            say(f"path {nA}x{nB} block {block} nu {nu}")
+            v, path = tw.twed_pair_path(*d, nu, lam, 1.0, "f64", block=block)
+            assert float(v.item()) == dist and np.array_equal(path.cpu().numpy(), want)
+            if block == 0 or min(nA, nB) < 650:
+                continue
+            ws = torch.empty(L.twed_pair_path_workspace_size(nA, nB, prm, block) - 1, dtype=torch.uint8, device="cuda")
+            out = torch.empty(1, dtype=torch.float64, device="cuda")
+            cells = torch.empty((nA + nB + 1, 2), dtype=torch.int64, device="cuda")
+            count = torch.empty(1, dtype=torch.int64, device="cuda")
+            say("  with four slots")
+            status = L.twed_pair_path(d[0].data_ptr(), d[1].data_ptr(), nA, d[2].data_ptr(), d[3].data_ptr(), nB, prm,
+                                      block, out.data_ptr(), cells.data_ptr(), count.data_ptr(), ws.data_ptr(),
+                                      ws.numel(), ctypes.c_void_p(torch.cuda.current_stream().cuda_stream))
+            assert status == 0 and float(out.item()) == dist
+            assert np.array_equal(cells[:int(count.item())].cpu().numpy(), want)
+
+
 def test_path_single_samples():
     """nA = 1 or nB = 1: the only admissible paths are a match then deletions."""
     for nA, nB in ((1, 1), (1, 9), (9, 1)):
