@@ -507,3 +507,39 @@ def test_pair_loss_over_workgroups(P):
         # order of the atomic additions differs
         _, g16, _ = run(base, t[:16])
         assert rel_norm(grad, g16) < 1e-2
+
+
+@pytest.mark.parametrize("n_db,n_cand", [(1, 1), (3, 2), (4095, 40), (4096, 4096), (4097, 33), (4099, 1000),
+                                         (12293, 64), (12293, 5000)])
+def test_candidate_selection_rounds_and_ties(n_db, n_cand):
+    # The selection reads 4,096 scores per round, four per thread, and takes the
+    # smallest scores, ties by the lowest id.  Seven distinct series repeated in
+    # a random order give seven groups of exactly equal scores, so the
+    # candidates follow from the order of the groups and the ids; with k = n_cand
+    # (at most 64 of them) the query returns the nearest of them.
+    rng = np.random.default_rng(n_db + n_cand)
+    kinds = [np.cumsum(rng.standard_normal(8 + 3 * i)).astype(np.float32) + 4 * i for i in range(7)]
+    which = rng.integers(0, len(kinds), n_db)
+    DB, offDB = pack([kinds[w] for w in which])
+    TDB = np.concatenate([np.arange(len(kinds[w]), dtype=np.float32) for w in which])
+    vec = knn.init_params(3)
+    Xk, offk = pack(kinds)
+    Q = kinds[2] + 0.5
+    both, off_both = pack(kinds + [Q])
+    emb = bf16(B.twed_embed_forward(dev(vec), dev(both), off_both).cpu().numpy()).astype(np.float64)
+    score = ((emb[:-1] - emb[-1]) ** 2).sum(axis=1)
+    gaps = np.diff(np.sort(score))
+    assert gaps.min() > 1e-3 * score.max()  # groups apart by far more than FP32 scores round
+    chosen = np.lexsort((np.arange(n_db), score[which]))[:n_cand]
+    D = oracle_dists(np.tile(Q, 1), np.arange(len(Q), dtype=np.float32), np.array([0, len(Q)]), Xk,
+                     np.concatenate([np.arange(len(s), dtype=np.float32) for s in kinds]), offk,
+                     np.array([(0, j) for j in range(len(kinds))]))
+    want = chosen[np.lexsort((chosen, D[which[chosen]]))]
+    k = min(n_cand, 64)
+    say(f"candidate selection: {n_cand} of {n_db}")
+    ix = index_for(DB, TDB, offDB, vec)
+    ids, _ = ix.query(dev(Q), dev(np.arange(len(Q), dtype=np.float32)), np.array([0, len(Q)], dtype=np.int64), k=k,
+                      n_cand=n_cand)
+    ids = ids.cpu().numpy()[0]
+    ix.close()
+    assert np.array_equal(ids, want[:k])
