@@ -253,8 +253,9 @@ twed_status plan_pair_sweep(Prec prec, const CostParams &cp, const twed_params *
     // through global memory; cell dumps use single-wave groups.
     // TWED_WAVEFRONT_GROUP (1, 4 or 8) and TWED_WAVEFRONT_SUB (in-group handoff
     // rows: 8, 16 or 32) override the choices for tuning runs.  A handoff every
-    // 32 rows beats 16 by 1 .. 3% and 8 by 8 .. 15% at every size measured (200
-    // to 10^6 samples): each costs the waves a poll and two fences.
+    // 32 rows beats 16 by up to 4% and 8 by 7 .. 16% (1,000 to 100,000 samples;
+    // 10^6 8-D samples run 0.4% faster with 16): each costs the waves two polls
+    // and the set-up of the next sub-chunk.
     plan->G = G;
     if (dump) plan->G = 1;
     if (const char *env = std::getenv("TWED_WAVEFRONT_GROUP")) {

@@ -49,43 +49,60 @@ constexpr int kNoRow = -0x40000000;
 // often not hidden: 3-D FP32 strips took 150 ns per step whatever their width.
 // Samples whose rings do not fit the LDS beside the rest keep the global reads.
 template <typename CT, int DIMT, int G>
-constexpr bool kRowRing = (3 * kWave + 1) * Row<CT, DIMT>::kStride * (int)sizeof(CT) * G <= 128 * 1024;
+constexpr bool kRowRing = (3 * kWave + 2) * Row<CT, DIMT>::kStride * (int)sizeof(CT) * G <= 128 * 1024;
 
 template <typename CT, typename AT, int DIMT, int G>
 struct GroupShared {
-    alignas(16) CT rows[G][kRowRing<CT, DIMT, G> ? (3 * kWave + 1) * Row<CT, DIMT>::kStride : 1];
+    alignas(16) CT rows[G][kRowRing<CT, DIMT, G> ? (3 * kWave + 2) * Row<CT, DIMT>::kStride : 1];
     Pair2<AT> ring[G > 1 ? G - 1 : 1][kRing + 1];  // boundary of wave w, read by wave w+1
-    Pair2<AT> in_stage[kWindow];                   // wave 0's left boundary, one global window
+    Pair2<AT> in_stage[kWindow + 1];               // wave 0's left boundary, one global window
     Pair2<AT> in_next[kWindow];                    // the next window, when it is there early
     Pair2<AT> out_stage[kRing + 1];                // wave G-1's right boundary before it goes out
     Pair2<AT> dummy[kWave + kMaxUnroll];           // takes the boundary writes of lanes 0 .. 62
-    uint32_t prod[G];                              // rows of that boundary published
-    uint32_t cons[G];                              // rows of wave w's left boundary consumed
+    int prod[G + 2];                               // rows of that boundary written; a sink; "all" (no wave to wait for)
+    int cons[G];                                   // rows of wave w's left boundary consumed
     uint32_t ticket[G];                            // ticket value seen by each wave (wave 0's is the claim)
 };
-
-__device__ __forceinline__ uint32_t load_lds_progress(const uint32_t *p)
-{
-    return wave_uniform(__hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP));
-}
 
 // Bounded wait until *p >= need (uniform across the wave).  A wave that gives
 // up marks the error word (the result strip then reports NaN) and carries
 // on, and once the word is set no wave waits any more (it is read every
 // kErrEvery polls), so every wave still reaches the end of the grid after at
 // most one time-out.
-template <bool LDS>
 __device__ __forceinline__ void wait_progress(const uint32_t *p, uint32_t need, uint32_t *err)
 {
     uint32_t polls = 0;
-    while ((LDS ? load_lds_progress(p) : load_progress(p)) < need) {
+    while (load_progress(p) < need) {
         if (polls % kErrEvery == kErrEvery - 1 && load_progress(err) != 0u) break;
         __builtin_amdgcn_s_sleep(1);
-        if (++polls > (LDS ? kMaxPollsLds : kMaxPollsGlobal)) {
+        if (++polls > kMaxPollsGlobal) {
             __hip_atomic_fetch_or(err, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             break;
         }
     }
+}
+
+// The same for a count in LDS: of the boundary rows that wave w - 1 of the group
+// has written or wave w has read.  Returns the count seen last.
+// All LDS operations of a compute unit are performed one after another, those of
+// a wave in its order, so rows written before a count are there for whoever has
+// read the count, and neither side waits for what else it has in flight (with
+// workgroup fences, which wait for every load and store: the 8-D pair of 10^6
+// samples 866 ms, now 855; 30,000 x 30,000 1-D in FP64 4.69 ms, now 4.63).
+__device__ __forceinline__ int wait_rows(const int *prod, int need, uint32_t *err)
+{
+    uint32_t polls = 0;
+    int seen;
+    while ((seen = __builtin_amdgcn_readfirstlane(
+                __hip_atomic_load(prod, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP))) < need) {
+        if (polls % kErrEvery == kErrEvery - 1 && load_progress(err) != 0u) break;
+        if (polls >= 4) __builtin_amdgcn_s_sleep(1);  // not yet under way: leave the SIMD to others
+        if (++polls > kMaxPollsLds) {
+            __hip_atomic_fetch_or(err, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            break;
+        }
+    }
+    return seen;
 }
 
 // Block boundaries and extra outputs of the tile sweep (TILE kernels only;
@@ -125,9 +142,9 @@ constexpr bool kStripCompiled = DIMT <= 16 || K <= 2;
 
 // One strip of 64*K columns swept by one wave.  Its left boundary (DP and X =
 // DP + e of column c0-1, per row) comes from the previous strip: through LDS
-// when that strip belongs to the same workgroup (handoff every kSub rows,
-// workgroup-scope release/acquire; kSub = 1 << sub_shift), through a global
-// slot and flag otherwise (every kWindow rows, agent scope).  Its right boundary goes the
+// when that strip belongs to the same workgroup (counted every kSub = 1 <<
+// sub_shift rows), through a global slot and flag otherwise (every kWindow
+// rows, agent-scope release/acquire).  Its right boundary goes the
 // same two ways to the next strip.
 //
 // rowsA points at row 0 of A, with kRowPad rows before it and kRowPadTail after
@@ -221,7 +238,7 @@ __device__ __forceinline__ void sweep_strip(GroupShared<CT, AT, DIMT, G> &sh, in
     // others is paid again in every strip along the front: dummy stores by the
     // other lanes, a branch, a load or the wait for stores at the next hand-over.
     // (Forward sweep of a path of 100,000 8-D samples: 53.4 ms with dummy stores,
-    // 38.8 with branches, now 34.)  Wide strips have no registers to spare.
+    // 38.8 with branches, now 36.)  Wide strips have no registers to spare.
     constexpr bool kCellsKept = TILE && K <= 2;
     Pair2<AT> tops[kCellsKept ? K : 1], kept[kCellsKept ? K : 1];
     if constexpr (kCellsKept) {
@@ -243,11 +260,15 @@ __device__ __forceinline__ void sweep_strip(GroupShared<CT, AT, DIMT, G> &sh, in
     // lstar hold columns beyond nB): the result is then in that lane's
     // registers, and the step loop carries no test for it.
     const int T_run = result_strip ? nA + lstar + 1 : T;
-    // The row of the next step is read one step ahead: from the wave's ring in
+    // Rows are read kAhead steps ahead of their use: from the wave's ring in
     // LDS, or from global memory (large samples).
     // (Wide strips of large samples, whose columns fill the registers, have none
     // left for the ring's loads.)
     constexpr bool RR = kRowRing<CT, DIMT, G> && S * (int)sizeof(CT) / 4 * K <= 96;
+    // How many steps ahead of its use a row and a boundary cell are read: an LDS
+    // read takes about as long as a narrow strip's step (1-D FP64: 1,000 x 1,000
+    // samples 181 -> 174 us, 30,000 x 30,000 4.88 -> 4.69 ms from one to two).
+    constexpr int kAhead = RR ? 2 : 1;
     constexpr int V = 16 / (int)sizeof(CT);
     typedef CT vec __attribute__((ext_vector_type(V)));
     CT *const rows_lds = &sh.rows[w][0];
@@ -264,7 +285,8 @@ __device__ __forceinline__ void sweep_strip(GroupShared<CT, AT, DIMT, G> &sh, in
         for (int v = 0; v < S / V; ++v) p[v] = fetched[v];
     };
     static_assert(kRowPad <= kRowPadTail && kWave <= kRowPadTail, "rows up to nA + 64 are read");
-    Row<CT, DIMT> cur, nxt;
+    Row<CT, DIMT> row[4];
+    Pair2<AT> nbs[2];
     const CT *row_at;  // row t - lane, the row lane `lane` works on at step t
     if constexpr (RR) {
         // lanes that have not reached row 0 sweep rows of zeros
@@ -275,7 +297,7 @@ __device__ __forceinline__ void sweep_strip(GroupShared<CT, AT, DIMT, G> &sh, in
         row_at = rows_lds;
     } else {
         row_at = rowsA - (ptrdiff_t)lane * S;
-        load_row<CT, DIMT>(row_at, 0, cur);
+        load_row<CT, DIMT>(row_at, 0, row[0]);
     }
     // Lane 0's left operands of the next step come from one LDS read at a
     // wave-uniform address (a broadcast: no cross-lane moves, no lane
@@ -287,6 +309,11 @@ __device__ __forceinline__ void sweep_strip(GroupShared<CT, AT, DIMT, G> &sh, in
     // whole windows are copied out.  Every lane executes that store, the others
     // into cells nobody reads: masking them off took five scalar instructions
     // and a branch per step, which a strip alone on its SIMD pays for in full.
+    // In-group hand-over: this wave's count goes to prod_out, the count of the
+    // wave before comes from prod_in.
+    const int *const prod_in = in_lds ? &sh.prod[w - 1] : &sh.prod[G + 1];
+    int *const prod_out = out_lds ? &sh.prod[w] : &sh.prod[G];
+    int counted = 0, consumed = 0;  // the last counts seen: of the wave before, and by the wave behind
     const bool has_in = in_global || in_lds;
     if (!has_in) sh.in_stage[lane] = Pair2<AT>{INF, INF};
     // boundary row t + 1 sits at in_src[t & in_mask]: ring slot t mod 128, or
@@ -320,7 +347,8 @@ __device__ __forceinline__ void sweep_strip(GroupShared<CT, AT, DIMT, G> &sh, in
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
             if (t0 + kWave < T_run) fetch(t0 + kWave);
             row_at = rows_lds + ((odd ? 2 * kWave : kWave) - lane) * S;
-            load_row<CT, DIMT>(row_at, 0, cur);
+            load_row<CT, DIMT>(row_at, 0, row[0]);
+            load_row<CT, DIMT>(row_at, 1, row[1]);
         }
         if (in_global && q == 0) {
             if (ahead) {
@@ -328,7 +356,7 @@ __device__ __forceinline__ void sweep_strip(GroupShared<CT, AT, DIMT, G> &sh, in
             } else {
                 if (flagged) {
                     const uint32_t need = (uint32_t)(t0 + kWindow < nA ? t0 + kWindow : nA);
-                    wait_progress<false>(in_flag, need, err);
+                    wait_progress(in_flag, need, err);
                     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
                 }
                 // rows t0 + 1 .. t0 + 64 of the boundary
@@ -351,18 +379,18 @@ __device__ __forceinline__ void sweep_strip(GroupShared<CT, AT, DIMT, G> &sh, in
                 ahead = true;
             }
         }
-        if (in_lds) {
-            // the rows this sub-chunk reads, t0 + 1 .. t0 + kSub, are in the ring
-            const uint32_t need = (uint32_t)(t0 + kSub < nA ? t0 + kSub : nA);
-            wait_progress<true>(&sh.prod[w - 1], need, err);
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+        {
+            // the rows this sub-chunk reads, t0 + 1 .. t0 + steps, are in the ring
+            const int need = t0 + steps < nA ? t0 + steps : nA;
+            if (counted < need) counted = wait_rows(prod_in, need, err);
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         }
         if (out_lds) {
             // this sub-chunk writes rows up to t0 + steps - 64 into the ring,
             // over the slots of rows up to 128 earlier: the next wave must
             // have read those
             const int last_w = t0 + steps - kWave;
-            if (last_w > kRing) wait_progress<true>(&sh.cons[w + 1], (uint32_t)(last_w - kRing), err);
+            if (consumed < last_w - kRing) consumed = wait_rows(&sh.cons[w + 1], last_w - kRing, err);
         }
 
         // This sub-chunk's first boundary cells: row t0 + 1 in, row t0 - 63 out
@@ -401,19 +429,20 @@ __device__ __forceinline__ void sweep_strip(GroupShared<CT, AT, DIMT, G> &sh, in
             }
         }
         uint32_t d_lo = 0, d_hi = 0;  // this sub-chunk's moves, the last step in the highest bits
-        // One step: sweep row t - lane with `use`, read row t + 1 - lane into
-        // `fill`; OFF is the step's place in its unrolled run.  Steps alternate
-        // the row buffers, so the row read ahead never has to be copied.  SP
+        // One step: sweep row t - lane with `use`, read row t + kAhead - lane into
+        // `fill`; OFF is the step's place in its unrolled run.  Steps take turns
+        // with the row buffers, so a row read ahead never has to be copied.  SP
         // (tile sweeps): lanes meet a row of interest in this sub-chunk; the
         // other sub-chunks run without testing for them at every step.  Where
         // cells are kept, the step only selects by lane.
-        auto step = [&]<bool SP, int OFF>(int i, Row<CT, DIMT> &use, Row<CT, DIMT> &fill) {
+        auto step = [&]<bool SP, int OFF>(int i, Row<CT, DIMT> &use, Row<CT, DIMT> &fill, Pair2<AT> &nb,
+                                         Pair2<AT> &nb_next) {
             static_assert(OFF < kMaxUnroll, "sh.dummy has room for this many");
             const int t = t0 + i;
-            load_row<CT, DIMT>(row_at, OFF + 1, fill);
-            // boundary row t + 1, which lane 0 meets at the next step (read
-            // before the cells so that its latency hides behind them)
-            const Pair2<AT> nb = in_at[OFF];
+            load_row<CT, DIMT>(row_at, OFF + kAhead, fill);
+            // boundary row t + kAhead, which lane 0 meets kAhead steps on (nb is
+            // row t + 1)
+            nb_next = in_at[OFF + kAhead - 1];
 
             AT left = sh_l, xl;
             if constexpr (TILE) {
@@ -515,17 +544,35 @@ __device__ __forceinline__ void sweep_strip(GroupShared<CT, AT, DIMT, G> &sh, in
         };
         auto run = [&]<bool SP>() {
             int i = 0;
-            for (; i + kMaxUnroll <= steps; i += kMaxUnroll) {
-                step.template operator()<SP, 0>(i, cur, nxt);
-                step.template operator()<SP, 1>(i + 1, nxt, cur);
-                step.template operator()<SP, 2>(i + 2, cur, nxt);
-                step.template operator()<SP, 3>(i + 3, nxt, cur);
-                advance(kMaxUnroll);
-            }
-            for (; i < steps; ++i) {  // the end of the sweep
-                step.template operator()<SP, 0>(i, cur, nxt);
-                cur = nxt;
-                advance(1);
+            if constexpr (RR) {
+                nbs[0] = in_at[0];
+                for (; i + kMaxUnroll <= steps; i += kMaxUnroll) {
+                    step.template operator()<SP, 0>(i, row[0], row[2], nbs[0], nbs[1]);
+                    step.template operator()<SP, 1>(i + 1, row[1], row[3], nbs[1], nbs[0]);
+                    step.template operator()<SP, 2>(i + 2, row[2], row[0], nbs[0], nbs[1]);
+                    step.template operator()<SP, 3>(i + 3, row[3], row[1], nbs[1], nbs[0]);
+                    advance(kMaxUnroll);
+                }
+                for (; i < steps; ++i) {  // the end of the sweep
+                    step.template operator()<SP, 0>(i, row[0], row[2], nbs[0], nbs[1]);
+                    row[0] = row[1];
+                    row[1] = row[2];
+                    nbs[0] = nbs[1];
+                    advance(1);
+                }
+            } else {
+                for (; i + kMaxUnroll <= steps; i += kMaxUnroll) {
+                    step.template operator()<SP, 0>(i, row[0], row[1], nbs[0], nbs[0]);
+                    step.template operator()<SP, 1>(i + 1, row[1], row[0], nbs[0], nbs[0]);
+                    step.template operator()<SP, 2>(i + 2, row[0], row[1], nbs[0], nbs[0]);
+                    step.template operator()<SP, 3>(i + 3, row[1], row[0], nbs[0], nbs[0]);
+                    advance(kMaxUnroll);
+                }
+                for (; i < steps; ++i) {  // the end of the sweep
+                    step.template operator()<SP, 0>(i, row[0], row[1], nbs[0], nbs[0]);
+                    row[0] = row[1];
+                    advance(1);
+                }
             }
         };
         if constexpr (TILE) {
@@ -537,17 +584,12 @@ __device__ __forceinline__ void sweep_strip(GroupShared<CT, AT, DIMT, G> &sh, in
 
         const int tend = t0 + steps;        // steps done so far
         const int last = tend - kWave;      // last boundary row complete
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         if (in_lds) {
             // rows up to tend have been read
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-            __hip_atomic_store(&sh.cons[w], (uint32_t)(tend < nA ? tend : nA), __ATOMIC_RELAXED,
-                               __HIP_MEMORY_SCOPE_WORKGROUP);
+            __hip_atomic_store(&sh.cons[w], tend, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
         }
-        if (out_lds && last >= 1) {
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-            __hip_atomic_store(&sh.prod[w], (uint32_t)(last < nA ? last : nA), __ATOMIC_RELAXED,
-                               __HIP_MEMORY_SCOPE_WORKGROUP);
-        }
+        __hip_atomic_store(prod_out, tend - kWave, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
         if (out_global && (q == (kWindow >> sub_shift) - 1 || tend >= T)) {
             // the window's rows, tend - 127 + lane for lanes kWave - (tend -
             // wb) .. 63, from out_stage to the slot (lanes without a row of
@@ -619,8 +661,9 @@ __device__ __forceinline__ void claim_groups(Shared &sh, uint32_t *ticket, int n
         const uint32_t mine = atomicAdd(ticket, threadIdx.x == 0 ? 1u : 0u);
         __hip_atomic_store(&sh.ticket[w], (uint32_t)__builtin_amdgcn_readlane((int)mine, 0), __ATOMIC_RELAXED,
                            __HIP_MEMORY_SCOPE_WORKGROUP);
-        __hip_atomic_store(&sh.prod[w], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        __hip_atomic_store(&sh.cons[w], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        __hip_atomic_store(&sh.prod[w], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        __hip_atomic_store(&sh.prod[G + 1], 0x7fffffff, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        __hip_atomic_store(&sh.cons[w], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
         __syncthreads();
         const int g = (int)__hip_atomic_load(&sh.ticket[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
         if (g >= nGroups) break;
