@@ -47,7 +47,7 @@ struct Sweep {
 };
 
 // The recurrence a sweep runs: kRecTwed, or a sibling (kRecDtw, kRecEdit,
-// kRecIndel; see twed_device.h), whose kernels exist for G in {4, 8} only.
+// kRecIndel; see twed_device.h).
 size_t sweep_scratch(int rec, Prec prec, const CostParams &cp, int K, int G)
 {
     return rec == kRecTwed ? tile_scratch_bytes(prec, cp, K, G) : dp_scratch_bytes(rec, prec, cp, K, G);
@@ -64,7 +64,6 @@ int sweep_workers(int rec, Prec prec, const CostParams &cp, int K, int G)
 // SIMDs, in groups of eight).
 Sweep tile_sweep(int rec, int strip_k, int64_t nA, int64_t nB, Prec prec, const CostParams &cp)
 {
-    const bool sib = rec != kRecTwed;
     const int64_t n_simds = simds();
     auto fits = [&](int K, int G) { return sweep_scratch(rec, prec, cp, K, G) == 0; };
     static const int any[] = {1, 2, 4, 8, 0};
@@ -82,13 +81,12 @@ Sweep tile_sweep(int rec, int strip_k, int64_t nA, int64_t nB, Prec prec, const 
             }
         }
         if (fits(K, 8)) G = 8;
-        else if (!fits(K, 4) && !sib) G = 1;
     }
-    // TWED_WAVEFRONT_GROUP (1, 4 or 8) overrides the group of plain TWED
-    // tile sweeps for tuning runs
+    // TWED_WAVEFRONT_GROUP (4 or 8) overrides the group of plain TWED tile
+    // sweeps for tuning runs
     if (const char *env = std::getenv("TWED_WAVEFRONT_GROUP")) {
         const int g = std::atoi(env);
-        if (!sib && (g == 1 || g == 4 || g == 8) && fits(K, g)) G = g;
+        if (rec == kRecTwed && (g == 4 || g == 8) && fits(K, g)) G = g;
     }
     return Sweep{K, G};
 }
