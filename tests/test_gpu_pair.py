@@ -336,6 +336,23 @@ def test_row_ring_edges_bitwise(dim, prec, monkeypatch):
         monkeypatch.delenv("TWED_WAVEFRONT_GROUP")
 
 
+@pytest.mark.parametrize("nA,nB,dim", [(4097, 1, 1), (3, 4097, 3), (4097, 4097, 1), (4608, 6145, 3), (8192, 8193, 1),
+                                       (2049, 10241, 8), (4500, 4100, 28)])
+def test_fp32_offset_over_the_workgroup(nA, nB, dim):
+    """Pairs longer than 4,096 samples get an FP32 cost offset, summed by 512
+    threads with up to four rows in flight each: lengths around a round of 512
+    and 2,048 rows, either series the longer, wide samples (one row in flight).
+    The result stays within the FP32 bar, is symmetric bit for bit, and agrees
+    to the bit between the two sweeps that use the offset."""
+    c = synth.random_pair(nA, nB, nA, nB, dim, irregular=True, nu=0.02, lam=0.6, p=2.0).astype(np.float32).astype(np.float64)
+    say(f"offset {nA}x{nB} dim {dim}")
+    v = gpu_twed(c.A, c.TA, c.B, c.TB, c.nu, c.lam, c.p, "f32")
+    want = oracle.twed(c.A, c.TA, c.B, c.TB, c.nu, c.lam, c.p)
+    assert abs(v - want) <= RTOL["f32"] * abs(want), (v, want)
+    assert gpu_twed(c.B, c.TB, c.A, c.TA, c.nu, c.lam, c.p, "f32") == v
+    assert gpu_twed(c.A, c.TA, c.B, c.TB, c.nu, c.lam, c.p, "f32", algo="diagonal") == v
+
+
 def test_strip_groups_long_pair_vs_oracle(monkeypatch):
     """A pair long enough for many LDS sub-chunks and global windows, in
     groups of 8, against the FP64 oracle (FP32 costs with FP64 accumulators)."""
