@@ -224,6 +224,12 @@ struct ChainShared {
     int start[kChainMax + 1];    // its place in the stream; the stream's length
 };
 
+__device__ __forceinline__ int64_t lane_value64(int64_t v, int lane)
+{
+    return (int64_t)(((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)((uint64_t)v >> 32), lane) << 32) |
+                     (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(uint64_t)v, lane));
+}
+
 // Sweeps the chain described by sh.start and sh.base (E series of `rows`)
 // against the nB columns of rowsB.  Lane e gets DP(nA_e, nB) of series e.
 template <typename CT, typename AT, int DIMT, int PM, int K>
@@ -258,15 +264,23 @@ __device__ __forceinline__ AT sweep_chain(ChainShared<CT, DIMT> &sh, const CT *_
     vec fetched[S / V];
     int fe = 0;  // the series that holds stream row g
     uint32_t g = lane;
+    const int64_t base0 = lane_value64(sh.base[0], 0);
     auto fetch = [&]() {
         const int gg = g < (uint32_t)total ? (int)g : total - 1;
-        for (;;) {
-            const bool past = gg >= sh.start[fe + 1];
-            fe += past ? 1 : 0;
-            if (__ballot(past) == 0) break;
+        int r = gg;
+        int64_t base = base0;
+        // (a pair alone needs no search; its table reads would be waited for every 64
+        // steps, which a cell of more components hides)
+        if (DIMT > 1 || E > 1) {
+            for (;;) {
+                const bool past = gg >= sh.start[fe + 1];
+                fe += past ? 1 : 0;
+                if (__ballot(past) == 0) break;
+            }
+            r = gg - sh.start[fe];
+            base = sh.base[fe];
         }
-        const int r = gg - sh.start[fe];
-        const vec *p = reinterpret_cast<const vec *>(rows + (sh.base[fe] + r) * S);
+        const vec *p = reinterpret_cast<const vec *>(rows + (base + r) * S);
 #pragma unroll
         for (int v = 0; v < S / V; ++v) fetched[v] = p[v];
         if (r == 0) {  // the pad row
@@ -323,10 +337,21 @@ __device__ __forceinline__ AT sweep_chain(ChainShared<CT, DIMT> &sh, const CT *_
             const int ev = t_in < t_out ? t_in : t_out;
             const int lim = ev < stop ? ev + 1 : stop;
             // two steps per iteration: the band registers alternate without copies
+            // 1-D samples: the barriers keep each row read a whole step ahead of its
+            // use.  Left to itself the compiler moves it next to its use, and a wave
+            // alone on its SIMD waits out the LDS latency in every second step (780
+            // pairs of 400 FP64 samples 104 us, now 96; of 1,000 391, now 351).
+            // Wider samples lose more by keeping the steps apart (20,000 pairs of 310
+            // 4-D FP32 samples 955 us without, 1,049 with).
+            auto ahead = [] {
+                if constexpr (DIMT == 1) __builtin_amdgcn_sched_barrier(0);
+            };
             for (; t + 2 <= lim; t += 2) {
                 load_row<CT, DIMT>(pr, 1, rb);
+                ahead();
                 step(ra);
                 load_row<CT, DIMT>(pr, 2, ra);
+                ahead();
                 step(rb);
                 pr += 2 * S;
             }
@@ -374,12 +399,6 @@ __device__ __forceinline__ AT chain_dispatch(int k, ChainShared<CT, DIMT> &sh, c
         if (k == K) return sweep_chain<CT, AT, DIMT, PM, K>(sh, rows, E, rowsB, nB, ca);
         return chain_dispatch<CT, AT, DIMT, PM, K + 1, KHI>(k, sh, rows, E, rowsB, nB, ca);
     }
-}
-
-__device__ __forceinline__ int64_t lane_value64(int64_t v, int lane)
-{
-    return (int64_t)(((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)((uint64_t)v >> 32), lane) << 32) |
-                     (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(uint64_t)v, lane));
 }
 
 // Waves per SIMD a chain kernel is held to (the registers the compiler may use).
@@ -477,18 +496,24 @@ __global__ __launch_bounds__(64, (chain_waves<CT, AT, DIMT, KHI>())) void batch_
                 ++item;
                 continue;
             }
-            // the stream: each series behind its pad row
+            // The stream: each series behind its pad row.  A pair alone needs no sum
+            // over the lanes.  Pair lists whose neighbours share nothing, 1-D FP32 in
+            // 128 .. 512 samples: 2,048 pairs 135 us with the sum and the table reads,
+            // now 127 (swept from global rows without a ring 131; 50,000 FP64 pairs in
+            // 20 .. 100 samples 341, 268 and 410 us).
             const int64_t nS = fix_x ? lb : la;
             int64_t end = lane < run ? nS + 1 : 0;
+            if (run > 1) {
 #pragma unroll
-            for (int d = 1; d < kWave; d <<= 1) {
-                const int64_t o = __shfl_up((long long)end, d, kWave);
-                end += lane >= d ? o : 0;
+                for (int d = 1; d < kWave; d <<= 1) {
+                    const int64_t o = __shfl_up((long long)end, d, kWave);
+                    end += lane >= d ? o : 0;
+                }
+                // (at most 2^30 rows in a chain of several)
+                const uint64_t fits = __ballot(end <= (int64_t(1) << 30));
+                const int most = fits == ~0ull ? kChainMax : __builtin_ctzll(~fits);
+                run = most < run ? (most > 1 ? most : 1) : run;
             }
-            // (at most 2^30 rows in a chain of several)
-            const uint64_t fits = __ballot(end <= (int64_t(1) << 30));
-            const int most = fits == ~0ull ? kChainMax : __builtin_ctzll(~fits);
-            run = most < run ? (most > 1 ? most : 1) : run;
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
             sh.start[0] = 0;
             sh.start[lane + 1] = (int)end;  // (entries past the run are not read)

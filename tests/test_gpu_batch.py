@@ -498,3 +498,41 @@ def test_short_query_row_split_bitwise(prec):
         plan.stage_y(Y, TY)
         assert np.array_equal(plan.run(q, tq).cpu().numpy().reshape(-1), want), (nq, dim, "staged")
         plan.close()
+
+
+def _distinct_order(rng, pairs):
+    """pairs in an order in which no two neighbours share a series (as far as a greedy pass finds one)."""
+    left = [tuple(p) for p in rng.permutation(pairs)]
+    out = [left.pop()]
+    while left:
+        k = next((k for k in range(len(left) - 1, -1, -1)
+                  if left[k][0] != out[-1][0] and left[k][1] != out[-1][1]), len(left) - 1)
+        out.append(left.pop(k))
+    return np.array(out, dtype=np.int64)
+
+
+@pytest.mark.parametrize("dim,p,prec", [(1, 1.0, "f32"), (1, 1.0, "f64"), (1, 1.0, "f32_acc64"), (2, 2.0, "f64"),
+                                        (4, 2.0, "f32"), (8, 2.0, "f32_acc64")])
+def test_pairs_without_common_neighbours_bitwise(dim, p, prec):
+    # Lists whose neighbouring pairs share no series (each is a chain of one)
+    # and the same pairs sorted (chains of many), at lengths around the 64-row
+    # chunks and the columns per lane up to the widest of the sample width:
+    # every entry is twed_pair's, bit for bit.
+    rng = np.random.default_rng(73)
+    longest = tw.load_library().twed_batch_max_short_length(dim)
+    lens = [L for L in (1, 2, 63, 64, 65, 127, 128, 129, 200, 256, 257, 320, 384, 449, 512, 513, 700, 961, 1024)
+            if L <= longest] + [min(90, longest), min(40, longest)]
+    n = len(lens)
+    col = synth.pack([synth.walk(rng, L, dim) for L in lens], [synth.irregular_times(rng, L) for L in lens])
+    X, T = to_dev(col, prec)
+    kw = dict(nu=0.01, lam=0.5, p=p, precision=prec)
+    prs = np.array([(i, j) for i in range(n) for j in range(n) if i != j], dtype=np.int64)
+    want = {}
+    say(f"single pairs dim{dim} {prec}")
+    for i, j in prs[prs[:, 0] < prs[:, 1]]:
+        a, b = slice(col.off[i], col.off[i + 1]), slice(col.off[j], col.off[j + 1])
+        want[i, j] = want[j, i] = tw.twed_pair(X[a], T[a], X[b], T[b], 0.01, 0.5, p, prec).item()
+    for name, order in (("no neighbours in common", _distinct_order(rng, prs)), ("runs", prs)):
+        say(f"pair list dim{dim} {prec}: {name}")
+        got = tw.twed_batch(X, T, col.off, X, T, col.off, pairs=torch.as_tensor(order, device="cuda"), **kw)
+        assert np.array_equal(got.cpu().numpy(), np.array([want[i, j] for i, j in order]))
