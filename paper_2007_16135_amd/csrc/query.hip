@@ -54,7 +54,7 @@ inline int query_pitch(int dim, int dimt, int elem, bool raw)
     return (units | 1) * v;
 }
 
-// RM: rows a wave can own.
+// RM: rows a wave owns (the last wave that has rows maybe fewer).
 template <typename CT, typename AT, int DIMT, int PM, bool RAW, int RM>
 __global__ __launch_bounds__(kWave *kQueryWaves, RM <= 7 ? 4 : 3) void batch_query_kernel(
     const CT *__restrict__ rowsQ, int nQ, const CT *__restrict__ rowsY, const CT *__restrict__ Yraw,
@@ -72,7 +72,13 @@ __global__ __launch_bounds__(kWave *kQueryWaves, RM <= 7 ? 4 : 3) void batch_que
     typedef const CT __attribute__((address_space(4))) *Scalars;
     extern __shared__ __align__(16) char query_lds[];
     CT *const stage = reinterpret_cast<CT *>(query_lds);  // two columns of 64 samples
-    __shared__ QueryHandOff<AT> hand[W - 1][2];
+    // The hand-over has two buffers in turn, or one, read behind the step's second
+    // barrier, for FP64 samples of more than 16 components: four workgroups then
+    // fit the LDS of a compute unit at every dimension (40,960 bytes each at 32).
+    // With two buffers three did, from 30 components on (staged rows: from 17 on),
+    // and 938 workgroups ran as 768 and 170.
+    constexpr int kHands = sizeof(CT) == 8 && DIMT > 16 ? 1 : 2;
+    __shared__ QueryHandOff<AT> hand[W - 1][kHands];
     __shared__ CT dels[4][kWave];  // deletion costs of the last four columns
     __shared__ int64_t place[2][kWave];  // element of every lane's sample in Y (or rowsY)
     const int tid = threadIdx.x, lane = tid & (kWave - 1);
@@ -93,10 +99,9 @@ __global__ __launch_bounds__(kWave *kQueryWaves, RM <= 7 ? 4 : 3) void batch_que
     }
     maxL = __builtin_amdgcn_readfirstlane(maxL);
     // rows of this wave: row r of [RM - nr, RM) is query row row0 + r
-    const int R = (nQ + W - 1) / W;
-    const int nr = nQ - w * R < R ? nQ - w * R : R;  // may be <= 0 (fewer rows than waves)
-    const int row0 = w * R + 1 - (RM - nr);
-    const int last_wave = (nQ - 1) / R;
+    const int nr = nQ - w * RM < RM ? nQ - w * RM : RM;  // may be <= 0 (this wave only stages samples)
+    const int row0 = w * RM + 1 - (RM - nr);
+    const int last_wave = (nQ - 1) / RM;
 
     // columns past a series' end repeat its last sample (nothing reads them)
     auto sample = [&](int j) { return yb + (j <= lb ? j : lb) - 1; };
@@ -193,13 +198,14 @@ __global__ __launch_bounds__(kWave *kQueryWaves, RM <= 7 ? 4 : 3) void batch_que
                 }
             }
             if constexpr (DELAY < W - 1) {
-                QueryHandOff<AT> &h = hand[DELAY][s & 1];
+                QueryHandOff<AT> &h = hand[DELAY][s % kHands];
                 h.dp[lane] = up[RM - 1];
                 h.x[lane] = xq[RM - 1];
             }
             if constexpr (DELAY == 0) dels[j & 3][lane] = del;
             if (DELAY == last_wave) res = j == lb ? up[RM - 1] : res;
         };
+        AT above_next = INF, x_next = INF;  // one buffer: DP and X of the row above, handed over at the step before
         const int steps = maxL + last_wave;
         for (int s = 1; s <= steps; ++s) {
             __syncthreads();
@@ -208,10 +214,10 @@ __global__ __launch_bounds__(kWave *kQueryWaves, RM <= 7 ? 4 : 3) void batch_que
             if constexpr (DELAY > 0) {
                 const int j = s - DELAY;
                 if (j >= 1 && j <= maxL && nr > 0) {
-                    const QueryHandOff<AT> &h = hand[DELAY - 1][(s - 1) & 1];
-                    const AT above = h.dp[lane], x_next = h.x[lane];
+                    const QueryHandOff<AT> &h = hand[DELAY - 1][(s - 1) % kHands];
+                    const AT above = kHands == 1 ? above_next : h.dp[lane], xn = kHands == 1 ? x_next : h.x[lane];
                     column(j, s, e[DELAY - 1], above, dels[j & 3][lane]);
-                    x_above = x_next;
+                    x_above = xn;
                 }
 #pragma unroll
                 for (int n = DELAY; n > 0; --n)
@@ -285,6 +291,10 @@ __global__ __launch_bounds__(kWave *kQueryWaves, RM <= 7 ? 4 : 3) void batch_que
                 }
             }
             __syncthreads();  // (the sample before this column's is read above)
+            if constexpr (DELAY > 0 && kHands == 1) {
+                above_next = hand[DELAY - 1][0].dp[lane];
+                x_next = hand[DELAY - 1][0].x[lane];
+            }
             if (s < maxL) put(s + 1);
         }
     };
@@ -311,8 +321,17 @@ hipError_t launch_batch_lane(Prec prec, const CostParams &cp, const void *rowsQ,
                                CostArgs<CT>::make(cp), (AT *)D);
             return hipGetLastError();
         };
-        // the rows a wave can own: the fewest compiled that hold the query
+        // The rows a wave owns: the fewest compiled that hold the query in four
+        // waves.  A wave computes the point costs of all RM rows, so the query's rows
+        // fill the first waves instead of being spread over the four (FP64, 60,000
+        // series of 20 .. 36 samples in R^32: 4 rows 247 us spread, now 138; 24 staged
+        // rows 328, now 289).  Two rows only for small samples: of more components the
+        // collection's samples bound a short query, and four rows in one wave leave
+        // the others to stage them (one row, 200,000 series in R^28 FP32: 262 us at
+        // two rows a wave, 220 at four).
         auto by_rows = [&]<bool RAW>() {
+            if constexpr (DIMT <= 4)
+                if (nQ <= 2 * kQueryWaves) return launch.template operator()<RAW, 2>();
             if (nQ <= 4 * kQueryWaves) return launch.template operator()<RAW, 4>();
             if (nQ <= 7 * kQueryWaves) return launch.template operator()<RAW, 7>();
             return launch.template operator()<RAW, kLaneMaxQuery / kQueryWaves>();

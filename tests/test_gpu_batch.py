@@ -536,3 +536,33 @@ def test_pairs_without_common_neighbours_bitwise(dim, p, prec):
         say(f"pair list dim{dim} {prec}: {name}")
         got = tw.twed_batch(X, T, col.off, X, T, col.off, pairs=torch.as_tensor(order, device="cuda"), **kw)
         assert np.array_equal(got.cpu().numpy(), np.array([want[i, j] for i, j in order]))
+
+
+@pytest.mark.parametrize("prec", ["f64", "f32", "f32_acc64"])
+def test_short_query_rows_per_wave_bitwise(prec):
+    # A wave owns two rows (up to four components), four, seven or eight: query
+    # lengths that fill one wave, one row more, and the last wave partly, for
+    # samples on both sides of four and of sixteen components (one hand-over
+    # buffer for wide FP64 samples), read from the caller's arrays and staged
+    # once.  Every entry equals the pair-list sweep's bits.
+    rng = np.random.default_rng(79)
+    dt = torch.float64 if prec == "f64" else torch.float32
+    f = lambda a: torch.as_tensor(np.ascontiguousarray(a), dtype=dt, device="cuda")
+    for nq, dim, p in ((2, 1, 1.0), (3, 4, 2.0), (7, 2, 2.0), (8, 3, 1.0), (9, 4, 2.0), (4, 5, 2.0), (5, 16, 2.0),
+                       (8, 32, 2.0), (12, 30, 2.0), (13, 17, 3.0), (16, 32, 2.0), (21, 29, 2.0), (22, 32, 2.0),
+                       (28, 24, 1.0), (29, 28, 2.0), (32, 31, 2.0)):
+        lens = np.concatenate([[1, 3, 2], rng.integers(1, 50, 130)])
+        off = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+        Y, TY = f(rng.standard_normal((off[-1], dim)).cumsum(0)), f(np.cumsum(rng.exponential(1.0, off[-1])))
+        q, tq = f(rng.standard_normal((nq, dim)).cumsum(0)), f(np.cumsum(rng.exponential(1.0, nq)))
+        offq = np.array([0, nq], dtype=np.int64)
+        kw = dict(nu=0.05, lam=0.7, p=p, precision=prec)
+        say(f"query rows {prec} nq {nq} dim {dim}")
+        prs = torch.as_tensor(np.stack([np.zeros(len(lens)), np.arange(len(lens))], 1).astype(np.int64), device="cuda")
+        want = tw.twed_batch(q, tq, offq, Y, TY, off, pairs=prs, **kw).cpu().numpy()
+        got = tw.twed_batch(q, tq, offq, Y, TY, off, **kw).cpu().numpy().reshape(-1)
+        assert np.array_equal(got, want), (nq, dim)
+        plan = tw.BatchPlan(offq, off, dim=dim, nu=0.05, lam=0.7, p=p, precision=prec)
+        plan.stage_y(Y, TY)
+        assert np.array_equal(plan.run(q, tq).cpu().numpy().reshape(-1), want), (nq, dim, "staged")
+        plan.close()
