@@ -148,10 +148,12 @@ twed_status twed_pair_matrix(const void *A, const void *TA, int64_t nA,
                              void *workspace, size_t ws_bytes, hipStream_t stream);
 
 /* Measures the single-pair sweep configurations (strip width = columns per
- * lane, strips per workgroup) on this pair -- a prefix of A of up to 262,144
- * samples against all of B -- and remembers the fastest for this precision,
- * dimension, distance and nB in a host-side, process-wide cache; later
- * twed_pair calls with strip_k == 0 and the same key use it.  Arguments as
+ * lane, strips per workgroup) on this pair -- all of B against A, or, where A
+ * is longer than 262,144 samples, against two prefixes of it, from which the
+ * time of all of A follows -- and remembers the fastest for this precision,
+ * dimension, distance, nB and the power of two below nA in a host-side,
+ * process-wide cache; later twed_pair calls with strip_k == 0 and the same key
+ * use it.  Arguments as
  * twed_pair (the same workspace size); the chosen values are written to
  * *strip_k and *group when those are not NULL.  Synchronises `stream`.
  * Results never depend on the configuration (every cell is evaluated with
@@ -388,7 +390,9 @@ twed_status twed_batch_plan_config(const twed_batch_plan *plan, int32_t *chunk, 
 /* Writes the tuning cache (single-pair choices of twed_pair_tune and batch
  * choices of twed_batch_plan_tune) to a text file, or merges such a file
  * into it, so that measurements survive the process.  Entries carry the
- * device they were measured on and apply only to that kind of device.
+ * device they were measured on and apply only to that kind of device.  Entries
+ * of earlier libraries, which lack the length class of A, are loaded and saved
+ * again but not used.
  * Errors: TWED_ERR_INVALID for a NULL path, a file that cannot be opened or
  * written, or (load) a malformed file, in which case nothing is merged. */
 twed_status twed_tune_save(const char *path);

@@ -143,10 +143,11 @@ PairLayout pair_layout(char *base, int64_t nA, int64_t nB, const twed_params *pr
 //
 // A single-pair sweep is configured by the strip width K (columns per lane),
 // the group size G (strips per workgroup) and the in-group handoff interval.
-// The defaults come from occupancy rules; twed_pair_tune measures the
-// candidates on the caller's own pair and caches the fastest per
-// (precision, dimension, distance, nB), which later calls with strip_k = 0
-// use.
+// The defaults come from rules; twed_pair_tune measures the candidates on the
+// caller's own pair and caches the fastest per (precision, dimension, distance,
+// nB, power of two below nA), which later calls with strip_k = 0 use.  (The
+// length of A decides as much as that of B: narrow strips sweep a long A
+// fastest, wide strips, which are fewer, a short one.)
 struct SweepChoice {
     int K, G, sub_shift;
 };
@@ -164,7 +165,13 @@ std::string device_id()
     return arch + "-cu" + std::to_string(prop.multiProcessorCount);
 }
 
-using TuneKey = std::tuple<std::string, int, int, int, int64_t>;
+int floor_log2(double v) { return v < 2.0 ? 0 : (int)std::floor(std::log2(v)); }
+
+// Device, precision, compiled dimension, distance, nB and floor(log2(nA)); the
+// last is kAnyLength for entries of files that do not hold it, which are kept
+// for the next save but not used.
+using TuneKey = std::tuple<std::string, int, int, int, int64_t, int>;
+constexpr int kAnyLength = -1;
 
 std::mutex &tune_mutex()
 {
@@ -178,10 +185,15 @@ std::map<TuneKey, SweepChoice> &tune_cache()
     return c;
 }
 
-bool tuned_choice(Prec prec, const CostParams &cp, int64_t nB, SweepChoice *out)
+TuneKey tune_key(Prec prec, const CostParams &cp, int64_t nA, int64_t nB)
+{
+    return TuneKey{device_id(), (int)prec, cp.dimt, cp.pm, nB, floor_log2((double)nA)};
+}
+
+bool tuned_choice(Prec prec, const CostParams &cp, int64_t nA, int64_t nB, SweepChoice *out)
 {
     std::lock_guard<std::mutex> lock(tune_mutex());
-    const auto it = tune_cache().find(TuneKey{device_id(), (int)prec, cp.dimt, cp.pm, nB});
+    const auto it = tune_cache().find(tune_key(prec, cp, nA, nB));
     if (it == tune_cache().end()) return false;
     *out = it->second;
     return true;
@@ -236,7 +248,7 @@ twed_status plan_pair_sweep(Prec prec, const CostParams &cp, const twed_params *
                             bool dump, const SweepChoice *force, SweepPlan *plan)
 {
     SweepChoice tuned{};
-    const bool have_tuned = !force && !dump && prm->strip_k == 0 && tuned_choice(prec, cp, nB, &tuned);
+    const bool have_tuned = !force && !dump && prm->strip_k == 0 && tuned_choice(prec, cp, nA, nB, &tuned);
     int K = 0, G = 0;
     choose_layout(prm, nA, nB, prec, cp, &K, &G);
     if (force) K = force->K;
@@ -515,8 +527,6 @@ std::map<BatchKey, BatchConfig> &batch_cache()
     static std::map<BatchKey, BatchConfig> c;
     return c;
 }
-
-int floor_log2(double v) { return v < 2.0 ? 0 : (int)std::floor(std::log2(v)); }
 
 struct BatchPlan {
     twed_params prm;
@@ -942,9 +952,11 @@ static twed_status twed_pair_tune_body(const void *A, const void *TA, int64_t nA
     uint32_t *flags = (uint32_t *)L.zero;
     uint32_t *tail = flags + L.nflags;
     hipError_t e;
-    // the cost per row is uniform, so a prefix of A long enough to cover the
-    // pipeline's fill and drain ranks the candidates
-    const int64_t rows = std::min<int64_t>(nA, 262144);
+    // A long A is measured on a prefix and half of it: a sweep's time is its
+    // pipeline's fill plus a constant per row, so the two give that of all nA
+    // rows (the prefix alone would weigh the fill too much and favour few, wide
+    // strips).
+    const int64_t rows = std::min<int64_t>(nA, 262144), half = rows / 2;
     e = launch_stage(prec, cp, B, TB, nullptr, 1, nB, nB, nB + 1, L.rowsB, nullptr, 0, st);
     if (e != hipSuccess) return fail_hip(e, "staging launch");
     hipEvent_t ev0 = nullptr, ev1 = nullptr;
@@ -962,16 +974,27 @@ static twed_status twed_pair_tune_body(const void *A, const void *TA, int64_t nA
         for (int G : {8, 4, 1}) {
             if (G > 1 && !pair_kernel_fits(prec, cp, K, G)) continue;
             const SweepChoice c{K, G, kSubShift};
-            // restaging A zeroes the flags and the ticket for this run
-            e = launch_stage(prec, cp, A, TA, nullptr, 1, rows, rows, rows + 1, L.rowsA, flags, L.zero_words, st);
-            if (e == hipSuccess) e = hipEventRecord(ev0, st);
-            if (e != hipSuccess) break;
-            s = run_pair_sweep(prec, cp, &p1, L.rowsA, L.rowsB, rows, nB, L.bnd, flags, tail, &L, L.tmp_out,
-                               nullptr, st, &c);
-            if (s != TWED_OK) break;
-            if ((e = hipEventRecord(ev1, st)) != hipSuccess || (e = hipEventSynchronize(ev1)) != hipSuccess) break;
-            float ms = 0.f;
-            if ((e = hipEventElapsedTime(&ms, ev0, ev1)) != hipSuccess) break;
+            // time of the first n rows of A against B (s or e set on failure)
+            auto time_of = [&](int64_t n) -> float {
+                float t = 0.f;
+                // restaging A zeroes the flags and the ticket for this run
+                e = launch_stage(prec, cp, A, TA, nullptr, 1, n, n, n + 1, L.rowsA, flags, L.zero_words, st);
+                if (e == hipSuccess) e = hipEventRecord(ev0, st);
+                if (e != hipSuccess) return t;
+                s = run_pair_sweep(prec, cp, &p1, L.rowsA, L.rowsB, n, nB, L.bnd, flags, tail, &L, L.tmp_out,
+                                   nullptr, st, &c);
+                if (s != TWED_OK) return t;
+                if ((e = hipEventRecord(ev1, st)) == hipSuccess && (e = hipEventSynchronize(ev1)) == hipSuccess)
+                    e = hipEventElapsedTime(&t, ev0, ev1);
+                return t;
+            };
+            float ms = time_of(rows);
+            if (e != hipSuccess || s != TWED_OK) break;
+            if (nA > rows) {
+                const float ms_half = time_of(half);
+                if (e != hipSuccess || s != TWED_OK) break;
+                ms += std::max(0.f, ms - ms_half) * (float)((double)(nA - rows) / (double)(rows - half));
+            }
             if (best.K == 0 || ms < best_ms) {
                 best = c;
                 best_ms = ms;
@@ -986,7 +1009,7 @@ static twed_status twed_pair_tune_body(const void *A, const void *TA, int64_t nA
     if (best.K == 0) return fail(TWED_ERR_UNSUPPORTED, "no sweep configuration fits this pair");
     {
         std::lock_guard<std::mutex> lock(tune_mutex());
-        tune_cache()[TuneKey{device_id(), (int)prec, cp.dimt, cp.pm, nB}] = best;
+        tune_cache()[tune_key(prec, cp, nA, nB)] = best;
     }
     if (strip_k) *strip_k = best.K;
     if (group) *group = best.G;
@@ -1238,7 +1261,7 @@ twed_status twed_batch_plan_tune(twed_batch_plan *plan, const void *X, const voi
 }
 
 // Tuning cache file: a header line, then one line per entry,
-//   pair  <device> <precision> <dimt> <pm> <nB> <K> <G> <sub_shift>
+//   pair  <device> <precision> <dimt> <pm> <nB> <K> <G> <sub_shift> <log2 nA>
 //   batch <device> <precision> <dimt> <pm> <mode> <lx> <ly> <items> <chunk> <waves_per_cu> <lane_mode>
 static const char kTuneHeader[] = "libtwed-tune 1";
 
@@ -1251,10 +1274,12 @@ static twed_status twed_tune_save_body(const char *path)
         char line[512];
         for (const auto &kv : tune_cache()) {
             const auto &k = kv.first;
-            std::snprintf(line, sizeof line, "pair %s %d %d %d %lld %d %d %d\n", std::get<0>(k).c_str(),
+            std::snprintf(line, sizeof line, "pair %s %d %d %d %lld %d %d %d", std::get<0>(k).c_str(),
                           std::get<1>(k), std::get<2>(k), std::get<3>(k), (long long)std::get<4>(k), kv.second.K,
                           kv.second.G, kv.second.sub_shift);
             text += line;
+            if (std::get<5>(k) != kAnyLength) text += " " + std::to_string(std::get<5>(k));
+            text += "\n";
         }
         for (const auto &kv : batch_cache()) {
             const auto &k = kv.first;
@@ -1301,12 +1326,13 @@ static twed_status twed_tune_load_body(const char *path)
         int a[10];
         long long n = 0;
         if (std::sscanf(l.c_str(), "%15s", kind) != 1) { bad = true; break; }
+        a[6] = kAnyLength;
         if (std::strcmp(kind, "pair") == 0 &&
-            std::sscanf(l.c_str(), "pair %127s %d %d %d %lld %d %d %d", dev, &a[0], &a[1], &a[2], &n, &a[3], &a[4],
-                        &a[5]) == 8 &&
+            std::sscanf(l.c_str(), "pair %127s %d %d %d %lld %d %d %d %d", dev, &a[0], &a[1], &a[2], &n, &a[3],
+                        &a[4], &a[5], &a[6]) >= 8 &&
             (a[3] == 1 || a[3] == 2 || a[3] == 4 || a[3] == 8) && (a[4] == 1 || a[4] == 4 || a[4] == 8) &&
-            a[5] >= 3 && a[5] <= 5) {
-            pairs[TuneKey{dev, a[0], a[1], a[2], (int64_t)n}] = SweepChoice{a[3], a[4], a[5]};
+            a[5] >= 3 && a[5] <= 5 && a[6] >= kAnyLength) {
+            pairs[TuneKey{dev, a[0], a[1], a[2], (int64_t)n, a[6]}] = SweepChoice{a[3], a[4], a[5]};
         } else if (std::strcmp(kind, "batch") == 0 &&
                    std::sscanf(l.c_str(), "batch %127s %d %d %d %d %d %d %d %d %d %d", dev, &a[0], &a[1], &a[2],
                                &a[3], &a[4], &a[5], &a[6], &a[7], &a[8], &a[9]) == 11 &&

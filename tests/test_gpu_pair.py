@@ -477,3 +477,52 @@ def test_high_dimensional_points_vs_oracle(dim):
             say(f"dim {dim} {prec} K={k}")
             v = gpu_twed(c.A, c.TA, c.B, c.TB, c.nu, c.lam, c.p, prec, strip_k=k)
             assert abs(v - ref) <= tol * abs(ref), (dim, prec, k, v, ref)
+
+
+def _tune_device():
+    p = torch.cuda.get_device_properties(0)
+    return f"{p.gcnArchName.split(':')[0]}-cu{p.multi_processor_count}"
+
+
+def test_tuned_layout_serves_its_own_lengths(tmp_path):
+    """A tuned layout is used for pairs of its nB and of A's power-of-two class
+    only: strips of eight columns, right for a short A, must not be swept by a
+    long one.  Entries without A's class (files of earlier libraries) are kept
+    for the next save and not used."""
+    nB, short, long_ = 20000, 2000, 100000
+    cfg = lambda nA: tw.twed_pair_config(nA, nB, 1, precision="f64")
+    tw.twed_tune_clear()
+    rule = {nA: cfg(nA) for nA in (short, 3000, long_)}
+    assert rule[long_]["strip_k"] != 8
+    lines = ["libtwed-tune 1", f"pair {_tune_device()} 0 1 0 {nB} 8 4 5 10"]  # 2^10 <= nA < 2^11
+    path = tmp_path / "tune.txt"
+    path.write_text("\n".join(lines) + "\n")
+    tw.twed_tune_load(path)
+    got = cfg(short)
+    assert (got["strip_k"], got["group"]) == (8, 4)
+    assert cfg(3000) == rule[3000] and cfg(long_) == rule[long_]
+    out = tmp_path / "saved.txt"
+    tw.twed_tune_save(out)
+    assert out.read_text().splitlines() == lines
+    tw.twed_tune_clear()
+    lines[1] = lines[1].rsplit(" ", 1)[0]
+    path.write_text("\n".join(lines) + "\n")
+    tw.twed_tune_load(path)
+    assert all(cfg(nA) == c for nA, c in rule.items())
+    tw.twed_tune_save(out)
+    assert out.read_text().splitlines() == lines
+    tw.twed_tune_clear()
+
+
+def test_tuner_on_a_prefix_of_a_long_series():
+    """A longer than the measured prefix: the tuned call still gives the same bits."""
+    c = synth.random_pair(95, 96, 300000, 900, 1, irregular=True, nu=0.01, lam=0.5, p=1.0)
+    A, TA, B, TB = (dev(x, torch.float64) for x in (c.A, c.TA, c.B, c.TB))
+    tw.twed_tune_clear()
+    before = float(tw.twed_pair(A, TA, B, TB, c.nu, c.lam, c.p, "f64").item())
+    k, g = tw.twed_pair_tune(A, TA, B, TB, c.nu, c.lam, c.p, "f64")
+    say(f"tuner on 300000 x 900: K={k} G={g}")
+    got = tw.twed_pair_config(300000, 900, 1, 0.01, 0.5, 1.0, "f64")
+    assert (got["strip_k"], got["group"]) == (k, g)
+    assert float(tw.twed_pair(A, TA, B, TB, c.nu, c.lam, c.p, "f64").item()) == before
+    tw.twed_tune_clear()
