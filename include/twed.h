@@ -363,17 +363,20 @@ void twed_batch_plan_destroy(twed_batch_plan *plan);
  * "cuTWED Implementation Remarks").  A batch run is configured by: the
  * consecutive items a wave takes per work ticket (chunk), the resident
  * waves per compute unit, and, for a single query of at most 32 samples,
- * whether each lane sweeps a whole pair (lane_mode 1) or each wave does
+ * whether the query's rows are split over the waves of a workgroup that sweeps
+ * 64 pairs, one per lane (lane_mode 1), or each wave sweeps pairs one by one
  * (0).  By default rules choose them.  twed_batch_plan_tune runs the plan on
  * the given inputs (as twed_batch_plan_run, several times: D is
  * overwritten) under the rules' choice and then, one knob at a time, under
- * each candidate (lane mode; chunk 1..64; a quarter, half or three quarters
- * of the waves that fit), keeps the fastest (median of three runs) in the
- * plan, and caches it under the plan's size class: device (architecture and
- * compute units), precision, dimension, distance, mode (symmetric,
- * rectangular, pair list), and the mean series lengths of X and Y and the
- * number of pairs, each rounded down to a power of two.  Plans created
- * afterwards, and twed_batch calls, of the same class use the cached choice.
+ * each candidate (lane mode; and, except in lane mode 1, chunk 1..64 and a
+ * quarter, half or three quarters of the waves that fit), keeps the fastest
+ * (median of three runs) in the plan, and caches it under the plan's size
+ * class: device (architecture and compute units), precision, dimension,
+ * distance, mode (symmetric, rectangular, one short query, pair list), and the
+ * mean series lengths of X and Y and the number of pairs, each rounded down to
+ * a power of two.  Plans created afterwards, and twed_batch calls, of the same
+ * class use the cached choice; its number of waves only where their longest
+ * pairs need the same kernel.
  * Synchronises `stream`.  Results never depend on the configuration: every
  * entry is the same bits.  The chosen values go to *chunk, *waves_per_cu
  * and *lane_mode when those are not NULL (0 / 0 / -1 mean the rule).
@@ -391,8 +394,8 @@ twed_status twed_batch_plan_config(const twed_batch_plan *plan, int32_t *chunk, 
  * choices of twed_batch_plan_tune) to a text file, or merges such a file
  * into it, so that measurements survive the process.  Entries carry the
  * device they were measured on and apply only to that kind of device.  Entries
- * of earlier libraries, which lack the length class of A, are loaded and saved
- * again but not used.
+ * of earlier libraries, which lack the length class of A or the kernel class,
+ * are loaded and saved again but not used.
  * Errors: TWED_ERR_INVALID for a NULL path, a file that cannot be opened or
  * written, or (load) a malformed file, in which case nothing is merged. */
 twed_status twed_tune_save(const char *path);

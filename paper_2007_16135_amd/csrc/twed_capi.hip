@@ -515,11 +515,15 @@ BatchLayout batch_layout(char *base, int64_t totX, int64_t nX, int64_t maxX, int
 struct BatchConfig {
     int chunk = 0;         // items per ticket (0: rule)
     int waves_per_cu = 0;  // resident waves per compute unit (0: all that fit)
-    int lane_mode = -1;    // single short query: 1 lane per pair (1), wave per pair (0), rule (-1)
+    int lane_mode = -1;    // single short query: the query kernel (1), wave per pair (0), rule (-1)
+    int kclass = kAnyClass;  // kernel (BatchClass) the choice was measured on
+    static constexpr int kAnyClass = -1;
 };
 
-// Size class: device, precision, compiled dimension, distance, mode, and the
-// mean lengths of X and Y and the item count rounded down to powers of two.
+// Size class: device, precision, compiled dimension, distance, mode (with
+// kOneQuery for the plans that the query kernel takes), and the mean lengths of
+// X and Y and the item count rounded down to powers of two.
+constexpr int kOneQuery = 3;
 using BatchKey = std::tuple<std::string, int, int, int, int, int, int, int>;
 
 std::map<BatchKey, BatchConfig> &batch_cache()
@@ -547,16 +551,24 @@ int64_t batch_items(const BatchPlan &P)
     return P.list ? P.nPairs : (P.sym ? P.nX * (P.nX - 1) / 2 : P.nX * P.nY);
 }
 
+// A single query short enough for the query kernel (rectangular mode).
+bool lane_eligible(const BatchPlan &P) { return !P.sym && !P.list && P.nX == 1 && P.maxX <= kLaneMaxQuery; }
+
+// Columns per lane of the plan's widest pair, and the kernel that holds them.
+int64_t batch_k_need(const BatchPlan &P)
+{
+    return std::min<int64_t>((std::min(P.maxX, P.maxY) + kWaveLanes - 1) / kWaveLanes, batch_kmax(P.cp.dimt));
+}
+
+int batch_class(const BatchPlan &P) { return batch_class_for(batch_k_need(P)); }
+
 BatchKey batch_key(const BatchPlan &P)
 {
-    const int mode = P.list ? kPairList : (P.sym ? kSymmetric : kRect);
+    const int mode = P.list ? kPairList : (P.sym ? kSymmetric : (lane_eligible(P) ? kOneQuery : kRect));
     return BatchKey{device_id(), (int)P.prec, P.cp.dimt, P.cp.pm, mode,
                     floor_log2((double)P.totX / (double)P.nX), floor_log2((double)P.totY / (double)P.nY),
                     floor_log2((double)std::max<int64_t>(1, batch_items(P)))};
 }
-
-// A single query short enough for one lane per pair (rectangular mode).
-bool lane_eligible(const BatchPlan &P) { return !P.sym && !P.list && P.nX == 1 && P.maxX <= kLaneMaxQuery; }
 
 twed_status batch_prepare(const int64_t *offX, int64_t nX, const int64_t *offY, int64_t nY, bool sym, bool list,
                           int64_t nPairs, const twed_params *prm, void *workspace, size_t ws_bytes, BatchPlan &P)
@@ -609,8 +621,11 @@ twed_status batch_prepare(const int64_t *offX, int64_t nX, const int64_t *offY, 
     {
         std::lock_guard<std::mutex> lock(tune_mutex());
         const auto it = batch_cache().find(P.key);
-        if (it != batch_cache().end()) P.cfg = it->second;
+        if (it != batch_cache().end() && it->second.kclass != BatchConfig::kAnyClass) P.cfg = it->second;
     }
+    // a number of waves means something for the kernel it was measured on only
+    // (a size class holds plans whose longest pairs need different ones)
+    if (P.cfg.kclass != batch_class(P)) P.cfg.waves_per_cu = 0;
     return TWED_OK;
 }
 
@@ -696,8 +711,7 @@ twed_status batch_enqueue(const BatchPlan &P, const void *X, const void *TX, con
     // 98.6 ms in three; 1-D FP64, 500 series of 100 .. 500, 40 items per wave:
     // 3.71 ms in one, 3.95 ms in two).
     const int kmax = batch_kmax(cp.dimt);
-    const int64_t k_need = std::min<int64_t>((std::min(maxX, maxY) + kWaveLanes - 1) / kWaveLanes, kmax);
-    const int kclass = batch_class_for(k_need);
+    const int kclass = batch_class(P);
     // Rectangular chains share a series of X, or one of Y where only those fit
     // the lanes of the kernel or where Y is the smaller collection (longer
     // chains).
@@ -717,7 +731,7 @@ twed_status batch_enqueue(const BatchPlan &P, const void *X, const void *TX, con
         if (e != hipSuccess) return fail_hip(e, "diagonal zero launch");
     }
     if (b.nItems > 0 && lane) {
-        // one short query: a lane per pair
+        // one short query
         e = launch_batch_lane(prec, cp, L.rowsX, (int)maxX, L.rowsY, Y, TY, (const int64_t *)L.offY, nY, Dk, st);
         if (e != hipSuccess) return fail_hip(e, "batch launch");
     } else if (b.nItems > 0) {
@@ -1223,9 +1237,12 @@ static twed_status twed_batch_plan_tune_body(twed_batch_plan *plan, const void *
             if ((s = consider(t)) != TWED_OK) break;
         }
     }
-    if (s == TWED_OK) {
+    if (s == TWED_OK && !lanes) {  // (the query kernel's grid is its own)
+        // shares of what fits of the kernel that the launches use (a symmetric plan
+        // with pairs of every width splits the widest off)
         const int cus = std::max(1, device_simds() / 4);
-        const int per_cu = batch_max_workers(P.prec, P.cp) / cus;
+        const int cls = P.sym && batch_class(P) == kBatchAll ? kBatchNarrow : batch_class(P);
+        const int per_cu = batch_max_workers(P.prec, P.cp, cls) / cus;
         for (int w : {per_cu / 4, per_cu / 2, (3 * per_cu) / 4}) {
             if (w < 1) continue;
             BatchConfig t = best;
@@ -1239,6 +1256,7 @@ static twed_status twed_batch_plan_tune_body(twed_batch_plan *plan, const void *
         P.cfg = start;
         return s;
     }
+    best.kclass = batch_class(P);
     P.cfg = best;
     {
         std::lock_guard<std::mutex> lock(tune_mutex());
@@ -1262,7 +1280,8 @@ twed_status twed_batch_plan_tune(twed_batch_plan *plan, const void *X, const voi
 
 // Tuning cache file: a header line, then one line per entry,
 //   pair  <device> <precision> <dimt> <pm> <nB> <K> <G> <sub_shift> <log2 nA>
-//   batch <device> <precision> <dimt> <pm> <mode> <lx> <ly> <items> <chunk> <waves_per_cu> <lane_mode>
+//   batch <device> <precision> <dimt> <pm> <mode> <lx> <ly> <items> <chunk> <waves_per_cu> <lane_mode> <class>
+// Entries without the last value come from earlier kernels: kept, not used.
 static const char kTuneHeader[] = "libtwed-tune 1";
 
 static twed_status twed_tune_save_body(const char *path)
@@ -1283,11 +1302,13 @@ static twed_status twed_tune_save_body(const char *path)
         }
         for (const auto &kv : batch_cache()) {
             const auto &k = kv.first;
-            std::snprintf(line, sizeof line, "batch %s %d %d %d %d %d %d %d %d %d %d\n", std::get<0>(k).c_str(),
+            std::snprintf(line, sizeof line, "batch %s %d %d %d %d %d %d %d %d %d %d", std::get<0>(k).c_str(),
                           std::get<1>(k), std::get<2>(k), std::get<3>(k), std::get<4>(k), std::get<5>(k),
                           std::get<6>(k), std::get<7>(k), kv.second.chunk, kv.second.waves_per_cu,
                           kv.second.lane_mode);
             text += line;
+            if (kv.second.kclass != BatchConfig::kAnyClass) text += " " + std::to_string(kv.second.kclass);
+            text += "\n";
         }
     }
     FILE *f = std::fopen(path, "w");
@@ -1323,10 +1344,11 @@ static twed_status twed_tune_load_body(const char *path)
         }
         if (l.empty()) continue;
         char kind[16], dev[128];
-        int a[10];
+        int a[11];
         long long n = 0;
         if (std::sscanf(l.c_str(), "%15s", kind) != 1) { bad = true; break; }
         a[6] = kAnyLength;
+        a[10] = BatchConfig::kAnyClass;
         if (std::strcmp(kind, "pair") == 0 &&
             std::sscanf(l.c_str(), "pair %127s %d %d %d %lld %d %d %d %d", dev, &a[0], &a[1], &a[2], &n, &a[3],
                         &a[4], &a[5], &a[6]) >= 8 &&
@@ -1334,10 +1356,12 @@ static twed_status twed_tune_load_body(const char *path)
             a[5] >= 3 && a[5] <= 5 && a[6] >= kAnyLength) {
             pairs[TuneKey{dev, a[0], a[1], a[2], (int64_t)n, a[6]}] = SweepChoice{a[3], a[4], a[5]};
         } else if (std::strcmp(kind, "batch") == 0 &&
-                   std::sscanf(l.c_str(), "batch %127s %d %d %d %d %d %d %d %d %d %d", dev, &a[0], &a[1], &a[2],
-                               &a[3], &a[4], &a[5], &a[6], &a[7], &a[8], &a[9]) == 11 &&
-                   a[7] >= 0 && a[7] <= 4096 && a[8] >= 0 && a[8] <= 64 && a[9] >= -1 && a[9] <= 1) {
-            batches[BatchKey{dev, a[0], a[1], a[2], a[3], a[4], a[5], a[6]}] = BatchConfig{a[7], a[8], a[9]};
+                   std::sscanf(l.c_str(), "batch %127s %d %d %d %d %d %d %d %d %d %d %d", dev, &a[0], &a[1], &a[2],
+                               &a[3], &a[4], &a[5], &a[6], &a[7], &a[8], &a[9], &a[10]) >= 11 &&
+                   a[7] >= 0 && a[7] <= 4096 && a[8] >= 0 && a[8] <= 64 && a[9] >= -1 && a[9] <= 1 &&
+                   a[10] >= BatchConfig::kAnyClass) {
+            batches[BatchKey{dev, a[0], a[1], a[2], a[3], a[4], a[5], a[6]}] =
+                BatchConfig{a[7], a[8], a[9], a[10]};
         } else {
             bad = true;
             break;

@@ -566,3 +566,65 @@ def test_short_query_rows_per_wave_bitwise(prec):
         plan.stage_y(Y, TY)
         assert np.array_equal(plan.run(q, tq).cpu().numpy().reshape(-1), want), (nq, dim, "staged")
         plan.close()
+
+
+def _device_key():
+    p = torch.cuda.get_device_properties(0)
+    return f"{p.gcnArchName.split(':')[0]}-cu{p.multi_processor_count}"
+
+
+def _load_choice(tmp_path, line):
+    path = tmp_path / "choice.txt"
+    path.write_text(f"libtwed-tune 1\n{line}\n")
+    tw.twed_tune_load(path)
+
+
+def test_tuned_choice_belongs_to_its_kernel(tmp_path):
+    # Two symmetric plans of one size class (60 series, mean length 64 .. 127)
+    # whose longest pairs need different kernels: a cached number of waves
+    # applies to the kernel it was measured on, a cached chunk to both, and an
+    # entry that does not name its kernel to neither.  One short query is a
+    # class of its own.
+    short, wide = np.full(60, 100), np.concatenate([np.full(58, 80), [700, 700]])
+    off = lambda lens: np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    config = lambda *a: tw.BatchPlan(*a, precision="f32").config()
+    tw.twed_tune_clear()
+    line = f"batch {_device_key()} 1 1 0 0 6 6 10 5 14 -1"
+    _load_choice(tmp_path, line + " 4")  # class 4: pairs of at most 256 samples
+    assert config(off(short)) == (5, 14, -1)
+    assert config(off(wide)) == (5, 0, -1)
+    out = tmp_path / "saved.txt"
+    tw.twed_tune_save(out)
+    assert out.read_text().splitlines() == ["libtwed-tune 1", line + " 4"]
+    tw.twed_tune_clear()
+    _load_choice(tmp_path, line)
+    assert config(off(short)) == config(off(wide)) == (0, 0, -1)
+    tw.twed_tune_clear()
+    many = off(np.full(100, 20))
+    _load_choice(tmp_path, f"batch {_device_key()} 1 1 0 1 4 4 6 5 14 -1 4")  # rectangular, 64 .. 127 pairs
+    assert config(off([20, 20]), off(np.full(50, 20))) == (5, 14, -1)
+    assert config(off([20]), many) == (0, 0, -1)
+    tw.twed_tune_clear()
+
+
+def test_tuner_searches_the_kernel_that_runs():
+    # One short query: its kernel has no number of waves to choose.  Short
+    # pairs: the candidates are shares of what fits of their own kernel (28
+    # waves per compute unit for 1-D FP32), not of the widest one's (8).
+    rng = np.random.default_rng(83)
+    X, T, off = _walks(rng, list(rng.integers(20, 120, 400)), 1)
+    f = lambda a: torch.as_tensor(np.ascontiguousarray(a), dtype=torch.float32, device="cuda")
+    tw.twed_tune_clear()
+    q = tw.BatchPlan(np.array([0, 20]), off, precision="f32")
+    chunk, waves, lane = q.tune(f(X[:20]), f(T[:20]), f(X), f(T))
+    say(f"one query: chunk {chunk} waves {waves} lane mode {lane}")
+    assert lane == 0 or (chunk, waves) == (0, 0)
+    sym = tw.BatchPlan(off, precision="f32")
+    want = sym.run(f(X), f(T)).clone()
+    chunk, waves, _ = sym.tune(f(X), f(T))
+    say(f"400 short series: chunk {chunk} waves {waves}")
+    assert waves in (0, 7, 14, 21)
+    assert torch.equal(sym.run(f(X), f(T)), want)
+    q.close()
+    sym.close()
+    tw.twed_tune_clear()
