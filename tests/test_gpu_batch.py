@@ -628,3 +628,81 @@ def test_tuner_searches_the_kernel_that_runs():
     q.close()
     sym.close()
     tw.twed_tune_clear()
+
+
+@pytest.mark.parametrize("prec", ["f64", "f32", "f32_acc64"])
+def test_wide_chains_bitwise(prec, tmp_path):
+    # Chains of several pairs at 5 .. 16 columns per lane (series of 257 ..
+    # 1,024 samples; the default chunk is one pair here, so a chunk of five is
+    # loaded as a tuned choice): symmetric, along X, along Y and listed, every
+    # entry twed_pair's bits.
+    rng = np.random.default_rng(89)
+    lens = [257, 300, 320, 321, 384, 385, 448, 511, 512, 513, 577, 640, 641, 767, 896, 961, 1000, 1023, 1024]
+    n = len(lens)
+    col = synth.pack([synth.walk(rng, L, 1) for L in lens], [synth.irregular_times(rng, L) for L in lens])
+    X, T = to_dev(col, prec)
+    kw = dict(nu=0.01, lam=0.5, p=1.0, precision=prec)
+    want = np.zeros((n, n))
+    say(f"single pairs {prec}")
+    for i in range(n):
+        for j in range(i + 1, n):
+            a, b = slice(col.off[i], col.off[i + 1]), slice(col.off[j], col.off[j + 1])
+            want[i, j] = want[j, i] = tw.twed_pair(X[a], T[a], X[b], T[b], 0.01, 0.5, 1.0, prec).item()
+    off_diag = ~np.eye(n, dtype=bool)
+    prs = np.argwhere(off_diag)
+    code = {"f64": 0, "f32": 1, "f32_acc64": 2}[prec]
+    tw.twed_tune_clear()
+    for mode, items in ((0, n * (n - 1) // 2), (1, n * n), (1, 3 * n), (2, len(prs))):
+        _load_choice(tmp_path, f"batch {_device_key()} {code} 1 0 {mode} 9 9 {int(np.log2(items))} 5 0 -1 0")
+    assert tw.BatchPlan(col.off, precision=prec).config()[0] == 5
+    few = col.subset([4, 11, 18])
+    F, TF = to_dev(few, prec)
+    say(f"chains of five {prec}")
+    D = tw.twed_batch(X, T, col.off, **kw).cpu().numpy()
+    assert np.array_equal(D, want)
+    R = tw.twed_batch(X, T, col.off, X, T, col.off, **kw).cpu().numpy()
+    assert np.array_equal(R[off_diag], want[off_diag])
+    same = np.arange(n)[:, None] == np.array([4, 11, 18])[None]
+    R = tw.twed_batch(X, T, col.off, F, TF, few.off, **kw).cpu().numpy()  # along Y
+    assert np.array_equal(R[~same], want[:, [4, 11, 18]][~same])
+    R = tw.twed_batch(F, TF, few.off, X, T, col.off, **kw).cpu().numpy().T  # along X
+    assert np.array_equal(R[~same], want[:, [4, 11, 18]][~same])
+    for order in (prs, prs[np.lexsort((prs[:, 0], prs[:, 1]))]):
+        pl = torch.as_tensor(np.ascontiguousarray(order, dtype=np.int64), device="cuda")
+        got = tw.twed_batch(X, T, col.off, X, T, col.off, pairs=pl, **kw).cpu().numpy()
+        assert np.array_equal(got, want[order[:, 0], order[:, 1]])
+    tw.twed_tune_clear()
+
+
+@pytest.mark.parametrize("prec", ["f64", "f32", "f32_acc64"])
+def test_three_width_launches_bitwise(prec):
+    # Enough items that a symmetric batch runs its widths in three launches (9 ..
+    # 16, 5 .. 8 and up to 4 columns per lane): the matrix is symmetric, equals
+    # the pair list's, which runs one kernel for all widths, and its entries of
+    # every pair of width classes are twed_pair's bits.
+    rng = np.random.default_rng(97)
+    lens = np.concatenate([rng.integers(513, 620, 12), rng.integers(257, 513, 20), rng.integers(1, 40, 728)])
+    lens = rng.permutation(lens)
+    n = len(lens)
+    assert n * (n - 1) // 2 - 66 >= 64 * 4096  # waves of the 5 .. 8 column kernel: at most 16 a compute unit
+    X, T, off = _walks(rng, list(lens), 1)
+    dt = torch.float64 if prec == "f64" else torch.float32
+    X = torch.as_tensor(X, dtype=dt, device="cuda")
+    T = torch.as_tensor(T, dtype=dt, device="cuda")
+    kw = dict(nu=0.01, lam=0.5, p=1.0, precision=prec)
+    say(f"three launches {prec}: {n} series")
+    D = tw.twed_batch(X, T, off, **kw)
+    assert torch.equal(D, D.T) and bool((D.diagonal() == 0).all())
+    i, j = torch.triu_indices(n, n, 1)
+    prs = torch.stack([i, j], 1).contiguous().cuda()
+    say("  the same pairs listed")
+    L = tw.twed_batch(X, T, off, X, T, off, pairs=prs, **kw)
+    assert torch.equal(L, D[prs[:, 0], prs[:, 1]])
+    by = [np.flatnonzero(lens > 512), np.flatnonzero((lens > 256) & (lens <= 512)), np.flatnonzero(lens <= 256)]
+    for a in by:
+        for b in by:
+            for u, v in zip(rng.choice(a, 6), rng.choice(b, 6)):
+                if u != v:
+                    su, sv = slice(off[u], off[u + 1]), slice(off[v], off[v + 1])
+                    one = tw.twed_pair(X[su], T[su], X[sv], T[sv], 0.01, 0.5, 1.0, prec).item()
+                    assert D[u, v].item() == one, (lens[u], lens[v])

@@ -142,3 +142,54 @@ def test_dp_paths_long_and_wide_strips():
     cost = sum(1 if (i1 - i0) + (j1 - j0) == 1 else int(a[i1 - 1] != b[j1 - 1])
                for (i0, j0), (i1, j1) in zip(P[:-1], P[1:]))
     assert cost == float(v.item()) == orc.edit(a, b)
+
+
+@pytest.mark.parametrize("kind,prec,dim,nA,nB", [("dtw", "f32_acc64", 8, 1500, 8700), ("dtw", "f64", 8, 1200, 8700),
+                                                 ("dtw", "f64", 3, 1300, 8700), ("edit", "f64", 1, 3000, 6700),
+                                                 ("edit", "f32_acc64", 1, 2900, 6700), ("lcs", "f64", 1, 3000, 6700)])
+def test_four_columns_per_lane(kind, prec, dim, nA, nB):
+    """Lengths at which the width rule takes strips of four columns (its
+    estimate for two and for eight is a tenth longer; a call cannot force
+    four): several groups of four strips, the value that strips of one, two
+    and eight give, bit for bit, and the oracle's."""
+    rng = np.random.default_rng(nA + dim)
+    orc = oracle.get()
+    if kind == "dtw":
+        a, b = rng.standard_normal((nA, dim)).cumsum(0), rng.standard_normal((nB, dim)).cumsum(0)
+        if prec != "f64":
+            a, b = a.astype(np.float32).astype(np.float64), b.astype(np.float32).astype(np.float64)
+        want = orc.dtw(a, b, 2.0)
+    else:
+        a, b = tokens(rng, nA, 5), tokens(rng, nB, 5)
+        want = orc.edit(a, b) if kind == "edit" else orc.lcs(a, b)
+    A, B = dev(a, prec), dev(b, prec)
+    got = {}
+    for k in (0, 1, 2, 8):
+        say(f"{kind} {nA}x{nB} dim {dim} {prec} K={k}")
+        got[k] = float(tw.twed_dp(kind, A, B, p=2.0, precision=prec, strip_k=k).item())
+    assert got[0] == got[1] == got[2] == got[8]
+    assert abs(got[0] - want) <= {"f64": 1e-12, "f32_acc64": 1e-6}[prec] * want if kind == "dtw" else got[0] == want
+
+
+def test_dp_path_four_columns_per_lane():
+    """A path whose forward sweep takes strips of four columns (blocks of 512,
+    checkpoint columns at their edges): admissible, with the oracle's value."""
+    nA, nB = 3000, 6700
+    rng = np.random.default_rng(21)
+    orc = oracle.get()
+    a, b = tokens(rng, nA, 6), tokens(rng, nB, 6)
+    say(f"edit path {nA}x{nB}")
+    v, path = tw.twed_dp_path("edit", dev(a, "f64"), dev(b, "f64"), block=512)
+    P = path.cpu().numpy()
+    _check_path(P, nA, nB, True)
+    d, to = np.diff(P, axis=0), P[1:] - 1
+    cost = int(np.where(d.sum(1) == 1, 1, a[to[:, 0]] != b[to[:, 1]]).sum())
+    assert cost == float(v.item()) == orc.edit(a, b)
+    A, B = rng.standard_normal((nA, 1)).cumsum(0), rng.standard_normal((nB, 1)).cumsum(0)
+    say(f"dtw path {nA}x{nB}")
+    v, path = tw.twed_dp_path("dtw", dev(A, "f64"), dev(B, "f64"), p=1.0, block=512)
+    P = path.cpu().numpy()
+    _check_path(P, nA, nB, False)
+    want = orc.dtw(A, B, 1.0)
+    assert abs(float(v.item()) - want) <= 1e-12 * want
+    assert abs(np.abs(A[P[1:, 0] - 1, 0] - B[P[1:, 1] - 1, 0]).sum() - want) <= 1e-10 * want
