@@ -202,19 +202,25 @@ bool tuned_choice(Prec prec, const CostParams &cp, int64_t nA, int64_t nB, Sweep
 // ---- strips of two widths ---------------------------------------------------------------
 //
 // With every strip resident, strip s starts lag_s of its own steps after
-// strip s-1 and then runs nA + 63 steps: the lag is 64 + 16 inside a group
-// (the lane skew and the in-group handoff interval) and 64 + 64 where the
-// boundary leaves the group through a global window.  A step of K columns
-// per lane costs about K + 1/2 cells of time (the boundary shifts, loads and
-// stores of the step).  The sweep ends when its last strip of either width
-// ends.  choose_mixed_split returns the number s1 of wide strips of a layout
-// that minimises that end with at most `slots` strips in all (every strip
-// resident), or 0 when no split beats uniform strips of the wide width by
-// 1% (or when uniform strips would not all be resident either).
-int64_t choose_mixed_split(const MixedLayout &L, int64_t nA, int64_t nB, int64_t slots)
+// strip s-1 and then runs nA + 63 steps: the lag is the lane skew of 64 plus the
+// in-group handoff interval, and 64 + 64 where the boundary leaves the group
+// through a global window.  A step of K columns per lane costs about K + 1/4
+// cells of time (the boundary shifts, loads and stores of the step).  The sweep
+// ends when its last strip of either width ends.  choose_mixed_split returns
+// the number s1 of wide strips of a layout that minimises that end with at most
+// `slots` strips in all (every strip resident), or 0 when no split beats uniform
+// strips of the wide width by 1% (or when uniform strips would not all be
+// resident either).  8-D FP32/FP64 pairs of equal lengths, handoffs every 32
+// rows (ms, uniform / split chosen / range of six other splits that fit the
+// slots): 950,000 samples 822 / 811 (676) / 813..814; 900,000 774 / 767 (623) /
+// 767..769; 850,000 736 / 731 (626) / 725..730; 700,000 602 / 596 (522) /
+// 595..598; 10^6, where the slots allow 1,289 or more, 863 / 856 / 857.  The
+// optimum is flat; splitting at all gives 0.6 .. 1.4%.
+int64_t choose_mixed_split(const MixedLayout &L, int64_t nA, int64_t nB, int64_t slots, int sub_shift)
 {
     const int K = L.wide, K2 = L.narrow, G = L.group;
-    constexpr double h = 0.5, lag_in = 80.0, lag_out = 128.0;
+    constexpr double h = 0.25, lag_out = 128.0;
+    const double lag_in = 64.0 + (double)(1 << sub_shift);
     auto lags = [&](int64_t n) { return lag_in * (double)n + (lag_out - lag_in) * (double)(n / G); };
     const double run = (double)(nA + 63);
     const int64_t su = (nB + 64 * K - 1) / (64 * K);
@@ -306,7 +312,8 @@ twed_status plan_pair_sweep(Prec prec, const CostParams &cp, const twed_params *
             const int mworkers = wavefront_mixed_max_workers(prec, cp, m);
             if (mworkers <= 0) return fail(TWED_ERR_DEVICE, "occupancy query failed");
             const int64_t su = (nB + 64 * L.wide - 1) / (64 * L.wide);
-            int64_t s1 = forced > 0 ? forced : choose_mixed_split(L, nA, nB, (int64_t)mworkers * L.group);
+            int64_t s1 = forced > 0 ? forced : choose_mixed_split(L, nA, nB, (int64_t)mworkers * L.group,
+                                                                    plan->sub_shift);
             s1 = std::min<int64_t>(s1, su - 1);
             if (s1 <= 0) continue;
             plan->layout = m;
