@@ -1344,8 +1344,8 @@ hipError_t launch_pair_loss(const float *emb, const int32_t *pairs, const float 
                             float *demb, float *loss_sum, hipStream_t st)
 {
     if (P <= 0) return hipSuccess;
-    // four pairs per wave, and at most 4,096 workgroups
-    const int grid = std::min((P + 4 * kLossWaves - 1) / (4 * kLossWaves), 4096);
+    // four pairs per wave, and at most 4,096 workgroups (P may be 2^31 - 1)
+    const int grid = std::min((P - 1) / (4 * kLossWaves) + 1, 4096);
     hipLaunchKernelGGL(pair_loss_kernel, dim3(grid), dim3(64 * kLossWaves), 0, st, emb, pairs, target, P, nSeries,
                        1.0f / (float)P, demb, loss_sum);
     return hipGetLastError();

@@ -543,3 +543,18 @@ def test_candidate_selection_rounds_and_ties(n_db, n_cand):
     ids = ids.cpu().numpy()[0]
     ix.close()
     assert np.array_equal(ids, want[:k])
+
+
+def test_pair_count_at_its_limit():
+    """2^31 - 1 pairs, the most the call takes, all of them outside the
+    collection: accepted, zero loss and gradient."""
+    vec, _ = random_params(3)
+    X, off = pack(ragged_series(4)[:3])
+    P = 2 ** 31 - 1
+    say(f"loss and gradient of {P} pairs outside the collection")
+    pairs = torch.full((P, 2), -1, dtype=torch.int32, device="cuda")
+    target = torch.zeros(P, dtype=torch.float32, device="cuda")
+    loss, grad, _ = B.twed_embed_loss_grad(dev(vec), dev(X), off, pairs, target)
+    torch.cuda.synchronize()
+    assert float(loss.item()) == 0.0
+    assert float(grad.abs().max().item()) == 0.0
