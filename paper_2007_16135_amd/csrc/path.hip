@@ -146,10 +146,6 @@ __global__ __launch_bounds__(kWave) void walk_kernel(const char *__restrict__ di
         const int end = e_in - __builtin_clzll(ends << (63 - e_in));
         const int k_out = (end > stop ? end : stop + 2) >> 1;
         const int count = entered < 0 ? 0 : k_in - k_out + 1;
-        if (__ballot(entered >= 0 && end > stop && moves >> (end & ~1) & 1u && moves >> (end | 1) & 1u) != 0) {
-            status = -1;  // both bits: no move
-            break;
-        }
         const int upto = wave_prefix_sum(count), dn = __builtin_amdgcn_readlane(upto, kWave - 1);
         if (n + dn > cap) {
             status = -1;

@@ -234,32 +234,24 @@ __device__ __forceinline__ void lane_row(Lane<CT, AT, DIMT, K> &L, const Row<CT,
     xlast = L.xp[K - 1];
 }
 
-// lane_row for unshifted accumulators, also returning the move into each of
-// the K cells as byte j of the result: 0 the match, 1 the deletion in A (from
-// the cell above), 2 the deletion in B (from the cell on the left), ties
-// resolved in that order.  The cell values are those of lane_row.
-template <typename CT, typename AT, int DIMT, int PM, int K>
-__device__ __forceinline__ uint64_t lane_row_dirs(Lane<CT, AT, DIMT, K> &L, const Row<CT, DIMT> &a, AT &left,
+// lane_row of one column for unshifted accumulators, also returning the move
+// into the cell: 0 the match, 1 the deletion in A (from the cell above), 2 the
+// deletion in B (from the cell on the left), ties resolved in that order.  The
+// cell value is that of lane_row.
+template <typename CT, typename AT, int DIMT, int PM>
+__device__ __forceinline__ uint32_t lane_row_dirs(Lane<CT, AT, DIMT, 1> &L, const Row<CT, DIMT> &a, AT &left,
                                                   AT diag, AT &xlast, CT nu, CT p, CT invp)
 {
-    static_assert(!kShifted<AT> && K <= 8, "moves are recorded for FP64 accumulators, K <= 8");
-    const AT dela = (AT)a.del;
-    uint64_t code = 0;
-#pragma unroll
-    for (int j = 0; j < K; ++j) {
-        const CT dist = point_dist<DIMT, PM, CT>(a.x, L.bx[j], p, invp);
-        const AT e = (AT)fma_(nu, fabs_(a.t - L.bt[j]), dist);
-        const AT m = diag + e, u = L.up[j] + dela, l = left + L.bdel[j];
-        const AT v = dmin(dmin(m, u), l);
-        const uint64_t mv = (m <= u && m <= l) ? 0u : (u <= l ? 1u : 2u);
-        code |= mv << (8 * j);
-        diag = L.xp[j];
-        L.xp[j] = v + e;
-        L.up[j] = v;
-        left = v;
-    }
-    xlast = L.xp[K - 1];
-    return code;
+    static_assert(!kShifted<AT>, "moves are recorded for FP64 accumulators");
+    const CT dist = point_dist<DIMT, PM, CT>(a.x, L.bx[0], p, invp);
+    const AT e = (AT)fma_(nu, fabs_(a.t - L.bt[0]), dist);
+    const AT m = diag + e, u = L.up[0] + (AT)a.del, l = left + L.bdel[0];
+    const AT v = dmin(dmin(m, u), l);
+    L.xp[0] = v + e;
+    L.up[0] = v;
+    left = v;
+    xlast = L.xp[0];
+    return (m <= u && m <= l) ? 0u : (u <= l ? 1u : 2u);
 }
 
 // ---- sibling recurrences ----------------------------------------------------------
@@ -277,27 +269,26 @@ __device__ __forceinline__ uint64_t lane_row_dirs(Lane<CT, AT, DIMT, K> &L, cons
 // (The Rec enum is in twed_kernels.h.)
 
 template <typename CT, typename AT, int DIMT, int PM, int K, int REC, bool DIRS>
-__device__ __forceinline__ uint64_t lane_row_sibling(Lane<CT, AT, DIMT, K> &L, const Row<CT, DIMT> &a, AT &left,
+__device__ __forceinline__ uint32_t lane_row_sibling(Lane<CT, AT, DIMT, K> &L, const Row<CT, DIMT> &a, AT &left,
                                                      AT diag, AT &xlast, CT p, CT invp)
 {
-    static_assert(REC != kRecTwed && K <= 8, "sibling recurrences only");
-    uint64_t code = 0;
+    static_assert(REC != kRecTwed, "sibling recurrences only");
+    static_assert(!DIRS || K == 1, "moves are recorded for one column per lane");
+    uint32_t code = 0;
 #pragma unroll
     for (int j = 0; j < K; ++j) {
         const AT up = L.up[j];
         AT v;
-        uint64_t mv = 0;
         if constexpr (REC == kRecDtw) {
             const AT d = (AT)point_dist<DIMT, PM, CT>(a.x, L.bx[j], p, invp);
             v = d + dmin(dmin(diag, up), left);
-            if constexpr (DIRS) mv = (diag <= up && diag <= left) ? 0u : (up <= left ? 1u : 2u);
+            if constexpr (DIRS) code = (diag <= up && diag <= left) ? 0u : (up <= left ? 1u : 2u);
         } else {
             const AT sub = a.x[0] == L.bx[j][0] ? AT(0) : (REC == kRecEdit ? AT(1) : pinf<AT>());
             const AT m = diag + sub, u = up + AT(1), l = left + AT(1);
             v = dmin(dmin(m, u), l);
-            if constexpr (DIRS) mv = (m <= u && m <= l) ? 0u : (u <= l ? 1u : 2u);
+            if constexpr (DIRS) code = (m <= u && m <= l) ? 0u : (u <= l ? 1u : 2u);
         }
-        if constexpr (DIRS) code |= mv << (8 * j);
         diag = up;
         L.up[j] = v;
         L.xp[j] = v;

@@ -449,10 +449,9 @@ __device__ __forceinline__ void sweep_strip(GroupShared<CT, AT, DIMT, G> &sh, in
                 if constexpr (DIRS) {
                     uint32_t code;
                     if constexpr (REC == kRecTwed)
-                        code = (uint32_t)lane_row_dirs<CT, AT, DIMT, PM, K>(L, use, left, sh_xo, xl, ca.nu, ca.p, ca.invp);
+                        code = lane_row_dirs<CT, AT, DIMT, PM>(L, use, left, sh_xo, xl, ca.nu, ca.p, ca.invp);
                     else
-                        code = (uint32_t)lane_row_sibling<CT, AT, DIMT, PM, K, REC, true>(L, use, left, sh_xo, xl, ca.p,
-                                                                                ca.invp);
+                        code = lane_row_sibling<CT, AT, DIMT, PM, K, REC, true>(L, use, left, sh_xo, xl, ca.p, ca.invp);
                     d_lo = __builtin_amdgcn_alignbit(d_hi, d_lo, 2);
                     d_hi = __builtin_amdgcn_alignbit(code == 0 ? 1u : code & 2u, d_hi, 2);
                 } else {
