@@ -4,10 +4,11 @@
 // (series pair, diagonal entry) onto a 2-D grid and fills the whole distance
 // matrix; its section "Validation using Real Datasets" notes that the
 // symmetric case needs only the upper triangle.  Here each pair is swept by
-// one wave with the whole band in registers: the shorter series is spread
-// over the 64 lanes (K = ceil(n/64) columns per lane, K <= KMAX), the longer
-// one streams through them, and the three live diagonals never leave the
-// register file.  Waves pull pairs from an atomic ticket; in the symmetric
+// one wave with the whole band in registers: one series is spread over the 64
+// lanes (K = ceil(n/64) columns per lane, K <= KMAX), the other streams through
+// them, and the three live diagonals never leave the register file.  A pair
+// alone spreads its shorter series; pairs in a chain the one they share,
+// whichever is shorter.  Waves pull pairs from an atomic ticket; in the symmetric
 // mode the series are visited longest-first so the expensive pairs start
 // first and the cheap ones fill the tail.  Results are bitwise equal to the
 // single-pair sweep: both evaluate every cell with the same lane code, and

@@ -21,12 +21,13 @@
 // the same for every lane, loaded four rows ahead, and the lanes' samples are
 // read from LDS once for all rows of the wave. The samples are staged by the
 // whole workgroup, consecutive threads reading consecutive bytes, one column
-// ahead of their use. 28 samples in R^28 against 60,000 series, FP64: 386 ->
-// 252 us a call (FP32 315 -> 163); against 2,000 series 667 -> 240 us. Held to
-// 128 registers (seven rows a wave), four workgroups share a compute unit and
-// all 938 run at once: 252 us against 285 at 132 registers; eight rows do not
-// fit and run three to a unit. Ten rows a wave in three waves (fewer scalar
-// loads) took 274 us.
+// ahead of their use. 28 samples in R^28 against 60,000 series of 28, FP64: 377
+// -> 231 us a call; of 20 .. 36 samples, FP64 441 -> 285, FP32 343 -> 151; against
+// 2,000 series of 28 FP32 249 -> 83. Held to 128 registers (seven rows a wave),
+// four workgroups, four waves per SIMD, share a compute unit and all 938 run at
+// once: a tenth faster than at 132 registers; eight rows do not fit and run three
+// to a unit. Ten rows a wave in three waves (fewer scalar loads) took a tenth
+// longer.
 //
 // RAW: the series are read as the caller holds them (Y: dim components per
 // sample, TY: timestamps) instead of as staged rows, and each sample's deletion

@@ -61,7 +61,7 @@ int sweep_workers(int rec, Prec prec, const CostParams &cp, int K, int G)
 // Strip width and group of a sweep of nA x nB cells: the pair sweep's rule
 // (resident_strip_width, groups of four, while the strips fit one wave per
 // SIMD; beyond that the widest strip that leaves three strips for every four
-// SIMDs, in groups of eight).
+// SIMDs, in groups of eight), with kernels that have no scratch at all.
 Sweep tile_sweep(int rec, int strip_k, int64_t nA, int64_t nB, Prec prec, const CostParams &cp)
 {
     const int64_t n_simds = simds();

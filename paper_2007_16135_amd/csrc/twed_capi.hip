@@ -65,7 +65,10 @@ int device_simds()
 }
 
 // A kernel with at most this much scratch per lane keeps its step loop in
-// registers (a few words outside it may be spilled).
+// registers.  Three of the compiled kernels have some (20 or 28 bytes: FP64, 16
+// components, four columns per lane, and 32 components, one column, L1 and L2,
+// all in groups of eight); they read it back once per sub-chunk of 32 steps,
+// before and after its step loop.
 constexpr size_t kScratchAllowed = 32;
 
 bool pair_kernel_fits(Prec prec, const CostParams &cp, int K, int G)
@@ -515,7 +518,7 @@ BatchLayout batch_layout(char *base, int64_t totX, int64_t nX, int64_t maxX, int
 // therefore be captured in a HIP graph).
 // A batch run is configured by the number of consecutive items a wave takes
 // per work ticket, the resident waves per compute unit, and whether a single
-// short query runs one lane per pair.  The defaults come from rules;
+// short query runs the query kernel.  The defaults come from rules;
 // twed_batch_plan_tune measures the candidates on a plan's own inputs and
 // caches the fastest under the plan's size class, which later plans and
 // twed_batch calls of that class use.
@@ -558,7 +561,14 @@ int64_t batch_items(const BatchPlan &P)
     return P.list ? P.nPairs : (P.sym ? P.nX * (P.nX - 1) / 2 : P.nX * P.nY);
 }
 
-// A single query short enough for the query kernel (rectangular mode).
+// A single query short enough for the query kernel (rectangular mode).  The line
+// is what that kernel holds, not where it stops being the faster one: it sweeps
+// 64 pairs a workgroup, so few or long series leave it with little to run side by
+// side.  Against a wave per pair, FP64 and FP32, 1 .. 28 components and 1 .. 32
+// rows: 60,000 series of 20 .. 36 samples 1.2 .. 11 times as fast, 2,000 series of
+// 28 samples 0.9 .. 4 times, 60 series 0.3 .. 0.7 times, 500 series of 400 .. 600
+// samples 0.06 .. 0.2 times (twed_batch_plan_tune measures both and keeps the
+// faster).
 bool lane_eligible(const BatchPlan &P) { return !P.sym && !P.list && P.nX == 1 && P.maxX <= kLaneMaxQuery; }
 
 // Columns per lane of the plan's widest pair, and the kernel that holds them.

@@ -182,7 +182,7 @@ struct DiagonalArgs {
 };
 hipError_t launch_diagonal(Prec prec, const CostParams &cp, const DiagonalArgs &a, hipStream_t st);
 
-// Batched pairs: one wave per pair, shorter series across the lanes.
+// Batched pairs: a wave sweeps a pair, or a chain of pairs that share a series.
 enum BatchMode : int { kSymmetric = 0, kRect = 1, kPairList = 2 };
 struct BatchArgs {
     const void *rowsX, *rowsY;   // packed rows (with pad rows)
@@ -202,7 +202,7 @@ struct BatchArgs {
 // Pair widths (columns per lane K) a batch kernel sweeps; pairs outside its
 // range are left to another launch.  A kernel holds the registers of its
 // widest pairs, so the narrower kernels fit more waves per SIMD (1-D FP32:
-// eight, five, four and two for the widths up to 2, 4, 8 and 16).
+// seven, four and two for the widths up to 4, 8 and 16).
 enum BatchClass : int {
     kBatchAll = 0,     // K = 1 .. KMAX
     kBatchNarrow = 1,  // K = 1 .. min(8, KMAX)
@@ -223,9 +223,10 @@ int batch_kmax(int dimt);
 // Items per ticket for pairs of series of these mean lengths.
 int batch_default_chunk(Prec prec, int dimt, double mean_x, double mean_y, bool y_fixed, int64_t items, int workers);
 // One query of at most kLaneMaxQuery samples (staged rows rowsQ) against nY
-// series: one lane per pair, D[j] = TWED(query, Y_j); The
-// series are the staged rows rowsY, or, with Yraw non-null, the caller's
-// arrays Yraw (dim components per sample) and TYraw read directly.
+// series: D[j] = TWED(query, Y_j).  A workgroup sweeps 64 pairs, one per lane,
+// the query's rows split over its waves.  The series are the staged rows rowsY,
+// or, with Yraw non-null, the caller's arrays Yraw (dim components per sample)
+// and TYraw read directly.
 constexpr int kLaneMaxQuery = 32;
 hipError_t launch_batch_lane(Prec prec, const CostParams &cp, const void *rowsQ, int nQ, const void *rowsY,
                             const void *Yraw, const void *TYraw, const int64_t *offY, int64_t nY, void *D,
