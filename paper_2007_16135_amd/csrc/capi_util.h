@@ -85,6 +85,10 @@ twed_status sweep_long_listed_pairs(Prec prec, const CostParams &cp, const twed_
                                     int64_t nY, const int64_t *pairs, int64_t nPairs, void *state,
                                     int64_t maxlen, void *D, hipStream_t st);
 
+// Strips that are resident at once, one wave per SIMD; two of a compute unit's
+// workgroups of one strip fit its LDS.
+inline int64_t resident_slots(int64_t simds, int group) { return group == 1 ? simds / 2 : simds; }
+
 // Columns per lane of a strip sweep whose strips are all resident, one wave per
 // SIMD: the width in `widths` (ascending, 0 after the last) with the least
 // estimated time.  Strip s starts about 110 of its steps after strip s - 1 (the
@@ -97,9 +101,9 @@ twed_status sweep_long_listed_pairs(Prec prec, const CostParams &cp, const twed_
 // (FP64 1-D, 30,000 x 30,000: 5.7 ms at the two columns chosen, 6.9 at one,
 // 7.4 at eight; 5,000 x 100,000: 5.2 ms at eight, 8.8 at two; 100,000 x 5,000:
 // 9.3 ms at one, 10.7 at two, 13.6 at four.)  0 when even the widest needs more
-// strips than `simds`.  fits(K): the kernel keeps to registers.
+// strips than `slots`.  fits(K): the kernel keeps to registers.
 template <typename Fits>
-int resident_strip_width(const int *widths, int64_t nA, int64_t nB, Prec prec, const CostParams &cp, int64_t simds,
+int resident_strip_width(const int *widths, int64_t nA, int64_t nB, Prec prec, const CostParams &cp, int64_t slots,
                          Fits &&fits)
 {
     double q = prec == kF64 ? (cp.dimt == 1 ? 0.24 : 0.55 + 0.03 * cp.dimt) : 0.2 + 0.053 * cp.dimt;
@@ -109,7 +113,7 @@ int resident_strip_width(const int *widths, int64_t nA, int64_t nB, Prec prec, c
     for (; *widths; ++widths) {
         const int K = *widths;
         const int64_t S = (nB + 64 * K - 1) / (64 * K);
-        if (S > simds) continue;
+        if (S > slots) continue;
         const double t = ((double)nA + 110.0 * (double)S) * (1.0 + q * K);
         if ((best == 0 || t < best_t) && fits(K)) {
             best = K;

@@ -51,11 +51,10 @@ hipError_t dp_by_config(int rec, const CostParams &cp, int K, int G, Fn &&fn)
                     if constexpr (!kDpCompiled<DIMT, KK>) {
                         return hipErrorInvalidValue;
                     } else {
-                        switch (G) {
-                        case 4: return fn.template operator()<CT, AT, DIMT, PM, KK, 4, REC>();
-                        case 8: return fn.template operator()<CT, AT, DIMT, PM, KK, 8, REC>();
-                        default: return hipErrorInvalidValue;
-                        }
+                        constexpr int R = kResidentGroup<CT, DIMT, PM>;
+                        if (G == R) return fn.template operator()<CT, AT, DIMT, PM, KK, R, REC>();
+                        if (G == 8) return fn.template operator()<CT, AT, DIMT, PM, KK, 8, REC>();
+                        return hipErrorInvalidValue;
                     }
                 };
                 switch (K) {

@@ -59,28 +59,31 @@ int sweep_workers(int rec, Prec prec, const CostParams &cp, int K, int G)
 }
 
 // Strip width and group of a sweep of nA x nB cells: the pair sweep's rule
-// (resident_strip_width, groups of four, while the strips fit one wave per
-// SIMD; beyond that the widest strip that leaves three strips for every four
-// SIMDs, in groups of eight), with kernels that have no scratch at all.
+// (resident_strip_width, groups of resident_group, while the strips fit one wave
+// per SIMD; beyond that the widest strip that leaves three strips for every four
+// SIMDs, in groups of eight where four fit at all), with kernels that have no
+// scratch at all.
 Sweep tile_sweep(int rec, int strip_k, int64_t nA, int64_t nB, Prec prec, const CostParams &cp)
 {
     const int64_t n_simds = simds();
+    const int G4 = resident_group(prec, cp.dimt, cp.pm);
     auto fits = [&](int K, int G) { return sweep_scratch(rec, prec, cp, K, G) == 0; };
-    static const int any[] = {1, 2, 4, 8, 0};
+    const int any[] = {1, G4 == 4 ? 2 : 0, 4, 8, 0};  // (the pair sweep's reason for one column)
     const int one[] = {strip_k, 0};
-    int G = 4;
-    int K = resident_strip_width(one[0] > 0 ? one : any, nA, nB, prec, cp, n_simds, [&](int k) { return fits(k, 4); });
+    int G = G4;
+    int K = resident_strip_width(one[0] > 0 ? one : any, nA, nB, prec, cp, resident_slots(n_simds, G4),
+                                 [&](int k) { return fits(k, G4); });
     if (K == 0) {
         K = one[0] > 0 ? one[0] : 1;
-        if (one[0] <= 0) {
+        if (one[0] <= 0 && G4 == 4) {
             for (int k : {8, 4, 2}) {
-                if ((nB + 64 * k - 1) / (64 * k) * 4 >= n_simds * 3 && (fits(k, 8) || fits(k, 4))) {
+                if ((nB + 64 * k - 1) / (64 * k) * 4 >= n_simds * 3 && (fits(k, 8) || fits(k, G4))) {
                     K = k;
                     break;
                 }
             }
         }
-        if (fits(K, 8)) G = 8;
+        if (G4 == 4 && fits(K, 8)) G = 8;
     }
     // TWED_WAVEFRONT_GROUP (4 or 8) overrides the group of plain TWED tile
     // sweeps for tuning runs

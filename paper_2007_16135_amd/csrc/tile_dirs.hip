@@ -1,7 +1,8 @@
 // tile_dirs.hip -- sweeps of blocks that also record the move into every cell
 // (two bits per cell, for reading an alignment path back).  Kept apart from
 // tile.hip: the recording code needs registers that the plain tile kernels
-// then do not pay for.  Strips of one column per lane in groups of four.
+// then do not pay for.  Strips of one column per lane in groups of
+// kResidentGroup.
 #include "wavefront_impl.h"
 
 #include <algorithm>
@@ -10,8 +11,6 @@
 namespace twed {
 
 namespace {
-
-constexpr int kDirsGroup = 4;
 
 template <typename CT, typename AT>
 struct DirsBlock {
@@ -36,10 +35,11 @@ struct DirsBlocks {
 // streams, four ran at once at most (one hardware queue each), the walk among
 // them.
 template <typename CT, typename AT, int DIMT, int PM, int REC>
-__global__ __launch_bounds__(kWave * kDirsGroup) void dirs_kernel(DirsBlocks<CT, AT> blocks, CostArgs<CT> ca,
-                                                                 int sub_shift)
+__global__ __launch_bounds__((kWave * kResidentGroup<CT, DIMT, PM>)) void dirs_kernel(DirsBlocks<CT, AT> blocks,
+                                                                              CostArgs<CT> ca, int sub_shift)
 {
-    __shared__ GroupShared<CT, AT, DIMT, kDirsGroup> sh;
+    constexpr int G = kResidentGroup<CT, DIMT, PM>;
+    __shared__ GroupShared<CT, AT, DIMT, G> sh;
     const DirsBlock<CT, AT> &d = blocks.b[blockIdx.y];
     const int nStrips = (d.nB + kWave - 1) / kWave;
     TileIO<AT> io{};
@@ -47,8 +47,8 @@ __global__ __launch_bounds__(kWave * kDirsGroup) void dirs_kernel(DirsBlocks<CT,
     io.left = d.left;
     io.dummy = d.dummy;
     io.dirs = d.dirs;
-    claim_groups<kDirsGroup>(sh, d.ticket, nStrips, [&](int w, int g, int s) {
-        sweep_strip<CT, AT, DIMT, PM, 1, kDirsGroup, false, true, REC, true>(
+    claim_groups<G>(sh, d.ticket, nStrips, [&](int w, int g, int s) {
+        sweep_strip<CT, AT, DIMT, PM, 1, G, false, true, REC, true>(
             sh, w, g, s, s * kWave, d.rowsA, d.rowsB, d.nA, d.nB, ca, d.bnd, d.flags, d.ticket + 1, nStrips, CT(0),
             d.out, nullptr, sub_shift, io);
     });
@@ -85,12 +85,13 @@ hipError_t launch_dirs(int rec, Prec prec, const CostParams &cp, const DirsArgs 
     if (n <= 0) return hipSuccess;
     if (n > kMaxDirsBlocks) return hipErrorInvalidValue;
     return by_config(rec, prec, cp, [&]<typename CT, typename AT, int DIMT, int PM, int REC>() -> hipError_t {
+        constexpr int G = kResidentGroup<CT, DIMT, PM>;
         DirsBlocks<CT, AT> g{};
         int64_t groups = 0;
         for (int i = 0; i < n; ++i) {
             const DirsArgs &a = blocks[i];
             const int64_t strips = (a.nB + kWave - 1) / kWave;
-            groups = std::max(groups, (strips + kDirsGroup - 1) / kDirsGroup);
+            groups = std::max(groups, (strips + G - 1) / G);
             g.b[i] = DirsBlock<CT, AT>{(const CT *)a.rowsA,     (const CT *)a.rowsB, (const Pair2<AT> *)a.top,
                                        (const Pair2<AT> *)a.left, (Pair2<AT> *)a.bnd,  (Pair2<AT> *)a.dummy,
                                        a.flags,                 a.ticket,            (AT *)a.out,
@@ -99,7 +100,7 @@ hipError_t launch_dirs(int rec, Prec prec, const CostParams &cp, const DirsArgs 
         // (workgroups claim groups until none is left: a grid smaller than the
         // groups of one very wide block is enough)
         const int grid = (int)std::min<int64_t>(groups, 1024);
-        hipLaunchKernelGGL((dirs_kernel<CT, AT, DIMT, PM, REC>), dim3(grid, n), dim3(kWave * kDirsGroup), 0, st, g,
+        hipLaunchKernelGGL((dirs_kernel<CT, AT, DIMT, PM, REC>), dim3(grid, n), dim3(kWave * G), 0, st, g,
                            CostArgs<CT>::make(cp), kSubShift);
         return hipGetLastError();
     });

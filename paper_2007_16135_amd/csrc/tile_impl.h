@@ -22,11 +22,10 @@ hipError_t launch_tile_kg(const WavefrontArgs &a, const TileIO<AT> &io, const Co
 template <typename CT, typename AT, int DIMT, int PM, int K>
 hipError_t launch_tile_k(const WavefrontArgs &a, const TileIO<AT> &io, const CostParams &cp, hipStream_t st)
 {
-    switch (a.group) {
-    case 4: return launch_tile_kg<CT, AT, DIMT, PM, K, 4>(a, io, cp, st);
-    case 8: return launch_tile_kg<CT, AT, DIMT, PM, K, 8>(a, io, cp, st);
-    default: return hipErrorInvalidValue;
-    }
+    constexpr int G = kResidentGroup<CT, DIMT, PM>;
+    if (a.group == G) return launch_tile_kg<CT, AT, DIMT, PM, K, G>(a, io, cp, st);
+    if (a.group == 8) return launch_tile_kg<CT, AT, DIMT, PM, K, 8>(a, io, cp, st);
+    return hipErrorInvalidValue;
 }
 
 template <typename AT>
@@ -46,7 +45,7 @@ TileIO<AT> typed(const TileArgs &t)
 }
 
 // fn.template operator()<CT, AT, DIMT, PM, K>() for a compiled configuration of
-// cost type COST (FP64 accumulators; G = 4 or 8).
+// cost type COST (FP64 accumulators; G = kResidentGroup or 8).
 template <typename COST, typename Fn>
 hipError_t tile_by_config(const CostParams &cp, int K, Fn &&fn)
 {
@@ -83,7 +82,8 @@ size_t tile_scratch_as(const CostParams &cp, int K, int G)
 {
     size_t bytes = (size_t)-1;
     (void)tile_by_config<COST>(cp, K, [&]<typename CT, typename AT, int DIMT, int PM, int KK>() -> hipError_t {
-        if (G == 4) bytes = scratch_kg<CT, AT, DIMT, PM, KK, 4, true>();
+        constexpr int R = kResidentGroup<CT, DIMT, PM>;
+        if (G == R) bytes = scratch_kg<CT, AT, DIMT, PM, KK, R, true>();
         else if (G == 8) bytes = scratch_kg<CT, AT, DIMT, PM, KK, 8, true>();
         return hipSuccess;
     });
@@ -95,7 +95,8 @@ int tile_occupancy_as(const CostParams &cp, int K, int G)
 {
     int per_cu = 0;
     (void)tile_by_config<COST>(cp, K, [&]<typename CT, typename AT, int DIMT, int PM, int KK>() -> hipError_t {
-        if (G == 4) per_cu = occupancy_kg<CT, AT, DIMT, PM, KK, 4, true>();
+        constexpr int R = kResidentGroup<CT, DIMT, PM>;
+        if (G == R) per_cu = occupancy_kg<CT, AT, DIMT, PM, KK, R, true>();
         else if (G == 8) per_cu = occupancy_kg<CT, AT, DIMT, PM, KK, 8, true>();
         return hipSuccess;
     });

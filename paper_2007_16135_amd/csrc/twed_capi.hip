@@ -77,8 +77,13 @@ bool pair_kernel_fits(Prec prec, const CostParams &cp, int K, int G)
 }
 
 // Columns per lane and strips per workgroup of the wavefront sweep.  While the
-// strips fit one wave per SIMD, groups of four (a wave on each SIMD of a compute
-// unit) of the width that resident_strip_width picks.  Beyond that the widest
+// strips fit one wave per SIMD, groups of resident_group (four, a wave on each
+// SIMD of a compute unit) of the width that resident_strip_width picks.  Rows of
+// 17 .. 32 FP64 components take strips of one column, one to a workgroup, at any
+// length: only there does the ring of rows fit, beside the LDS the registers too
+// (32-D, ms of one column / two: 3,000 x 300 samples 1.00 / 2.1, 800 x 30,000
+// 16.8 / 18.5, 20,000 x 40,000 28.8 / 39; four strips to a workgroup without
+// rings 3.0, 41 and 74).  Beyond one wave per SIMD the widest
 // strip whose kernel keeps to registers (wide strips of high-dimensional or
 // general-Lp sweeps would spill) that still gives three strips for every four
 // SIMDs, in groups of eight where those keep to registers (eight waves put two
@@ -86,13 +91,15 @@ bool pair_kernel_fits(Prec prec, const CostParams &cp, int K, int G)
 void choose_layout(const twed_params *prm, int64_t nA, int64_t nB, Prec prec, const CostParams &cp, int *K, int *G)
 {
     const int64_t simds = device_simds();
-    static const int widths[] = {1, 2, 4, 8, 0};
+    const int G4 = resident_group(prec, cp.dimt, cp.pm);
+    const int widths[] = {1, G4 == 4 ? 2 : 0, 4, 8, 0};
     const int one[] = {prm->strip_k, 0};
-    *G = 4;
-    *K = resident_strip_width(prm->strip_k > 0 ? one : widths, nA, nB, prec, cp, simds,
-                              [&](int k) { return pair_kernel_fits(prec, cp, k, 4); });
+    *G = G4;
+    *K = resident_strip_width(prm->strip_k > 0 ? one : widths, nA, nB, prec, cp, resident_slots(simds, G4),
+                              [&](int k) { return pair_kernel_fits(prec, cp, k, G4); });
     if (*K > 0) return;
     *K = prm->strip_k > 0 ? prm->strip_k : 1;
+    if (G4 == 1) return;
     if (prm->strip_k <= 0) {
         for (int k : {8, 4, 2}) {
             if ((nB + 64 * k - 1) / (64 * k) * 4 >= simds * 3 && wavefront_scratch_bytes(prec, cp, k, 1) == 0) {

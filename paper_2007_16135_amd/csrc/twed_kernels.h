@@ -20,6 +20,19 @@ int dimt_for(int dim);
 // Elements per packed row for (precision, DIMT).
 int row_stride(Prec prec, int dimt);
 inline size_t cost_size(Prec p) { return p == kF64 ? 8 : 4; }
+// Strips per workgroup of a sweep with one wave per SIMD: four, a wave on each
+// SIMD of a compute unit, where four waves' rings of rows fit its LDS, else (17 ..
+// 32 FP64 components) one.  Without rings every lane reads its rows from global
+// memory, 17 KB a step and wave, and four waves on one compute unit wait for its
+// L1 (1.1 us a step instead of 0.33).  In general Lp (pm 2) a step's powers take
+// longer than that, and four with the shorter hand-over are the faster (32-D,
+// 300 x 3,000 samples: 75 ms against 89).
+constexpr int kRingRows = 194;
+constexpr int kRingBytes = 128 * 1024;
+inline int resident_group(Prec prec, int dimt, int pm)
+{
+    return pm == 2 || kRingRows * row_stride(prec, dimt) * (int)cost_size(prec) * 4 <= kRingBytes ? 4 : 1;
+}
 inline size_t acc_size(Prec p) { return p == kF32 ? 4 : 8; }
 
 struct CostParams {

@@ -49,11 +49,15 @@ constexpr int kNoRow = -0x40000000;
 // often not hidden: 3-D FP32 strips took 150 ns per step whatever their width.
 // Samples whose rings do not fit the LDS beside the rest keep the global reads.
 template <typename CT, int DIMT, int G>
-constexpr bool kRowRing = (3 * kWave + 2) * Row<CT, DIMT>::kStride * (int)sizeof(CT) * G <= 128 * 1024;
+constexpr bool kRowRing = kRingRows * Row<CT, DIMT>::kStride * (int)sizeof(CT) * G <= kRingBytes;
+static_assert(kRingRows == 3 * kWave + 2, "two chunks, one of them twice, and two rows read ahead");
+// resident_group of a kernel.
+template <typename CT, int DIMT, int PM>
+constexpr int kResidentGroup = kRowRing<CT, DIMT, 4> || PM == kLp ? 4 : 1;
 
 template <typename CT, typename AT, int DIMT, int G>
 struct GroupShared {
-    alignas(16) CT rows[G][kRowRing<CT, DIMT, G> ? (3 * kWave + 2) * Row<CT, DIMT>::kStride : 1];
+    alignas(16) CT rows[G][kRowRing<CT, DIMT, G> ? kRingRows * Row<CT, DIMT>::kStride : 1];
     Pair2<AT> ring[G > 1 ? G - 1 : 1][kRing + 1];  // boundary of wave w, read by wave w+1
     Pair2<AT> in_stage[kWindow + 1];               // wave 0's left boundary, one global window
     Pair2<AT> in_next[kWindow];                    // the next window, when it is there early
@@ -264,11 +268,20 @@ __device__ __forceinline__ void sweep_strip(GroupShared<CT, AT, DIMT, G> &sh, in
     // LDS, or from global memory (large samples).
     // (Wide strips of large samples, whose columns fill the registers, have none
     // left for the ring's loads.)
-    constexpr bool RR = kRowRing<CT, DIMT, G> && S * (int)sizeof(CT) / 4 * K <= 96;
+    constexpr int kRowWords = S * (int)sizeof(CT) / 4;
+    constexpr bool RR = kRowRing<CT, DIMT, G> && kRowWords * K <= 96;
+    // One row read ahead, not two, and steps kept apart, two to a turn: for rows of
+    // 17 .. 32 FP64 components, or the rows in flight alone fill the registers
+    // (32-D, 3,000 x 300 samples: 1.23 ms with two ahead and four to a turn, now
+    // 1.00; pairs in strips of two columns, which read no ring, keep four), and for
+    // more than eight components in general Lp, whose powers, inlined for every
+    // component of four steps, overrun the instruction cache (FP64 12-D, 10,000 x
+    // 800 samples: 68.7 ms, now 62.9).
+    constexpr bool kTwoSteps = (kRowWords > 64 && (RR || TILE)) || (PM == kLp && DIMT > 8);
     // How many steps ahead of its use a row and a boundary cell are read: an LDS
     // read takes about as long as a narrow strip's step (1-D FP64: 1,000 x 1,000
     // samples 181 -> 174 us, 30,000 x 30,000 4.88 -> 4.69 ms from one to two).
-    constexpr int kAhead = RR ? 2 : 1;
+    constexpr int kAhead = RR && !kTwoSteps ? 2 : 1;
     constexpr int V = 16 / (int)sizeof(CT);
     typedef CT vec __attribute__((ext_vector_type(V)));
     CT *const rows_lds = &sh.rows[w][0];
@@ -348,7 +361,7 @@ __device__ __forceinline__ void sweep_strip(GroupShared<CT, AT, DIMT, G> &sh, in
             if (t0 + kWave < T_run) fetch(t0 + kWave);
             row_at = rows_lds + ((odd ? 2 * kWave : kWave) - lane) * S;
             load_row<CT, DIMT>(row_at, 0, row[0]);
-            load_row<CT, DIMT>(row_at, 1, row[1]);
+            if constexpr (kAhead == 2) load_row<CT, DIMT>(row_at, 1, row[1]);
         }
         if (in_global && q == 0) {
             if (ahead) {
@@ -534,7 +547,7 @@ __device__ __forceinline__ void sweep_strip(GroupShared<CT, AT, DIMT, G> &sh, in
             out_at[OFF] = Pair2<AT>{left, xl};  // (lane 63: row t - 63 of the strip's right boundary)
             // Wide strips fill the SIMD by themselves; steps mixed with their
             // neighbours would only cost registers.
-            if constexpr (S * (int)sizeof(CT) / 4 * K > 96) __builtin_amdgcn_sched_barrier(0);
+            if constexpr (kRowWords * K > 96 || kTwoSteps) __builtin_amdgcn_sched_barrier(0);
         };
         auto advance = [&](int n) {
             row_at += n * S;
@@ -543,7 +556,7 @@ __device__ __forceinline__ void sweep_strip(GroupShared<CT, AT, DIMT, G> &sh, in
         };
         auto run = [&]<bool SP>() {
             int i = 0;
-            if constexpr (RR) {
+            if constexpr (kAhead == 2) {
                 nbs[0] = in_at[0];
                 for (; i + kMaxUnroll <= steps; i += kMaxUnroll) {
                     step.template operator()<SP, 0>(i, row[0], row[2], nbs[0], nbs[1]);
@@ -557,6 +570,18 @@ __device__ __forceinline__ void sweep_strip(GroupShared<CT, AT, DIMT, G> &sh, in
                     row[0] = row[1];
                     row[1] = row[2];
                     nbs[0] = nbs[1];
+                    advance(1);
+                }
+            } else if constexpr (kTwoSteps) {
+#pragma unroll 1
+                for (; i + 2 <= steps; i += 2) {
+                    step.template operator()<SP, 0>(i, row[0], row[1], nbs[0], nbs[0]);
+                    step.template operator()<SP, 1>(i + 1, row[1], row[0], nbs[0], nbs[0]);
+                    advance(2);
+                }
+                if (i < steps) {  // the end of the sweep
+                    step.template operator()<SP, 0>(i, row[0], row[1], nbs[0], nbs[0]);
+                    row[0] = row[1];
                     advance(1);
                 }
             } else {

@@ -252,3 +252,31 @@ def test_path_on_a_side_stream():
         d1, p1 = float(d1.item()), p1.cpu().numpy()
     assert d1 == d0
     assert np.array_equal(p1, p0)
+
+
+@pytest.mark.parametrize("dim,p", [(17, 2.0), (32, 1.0), (24, 3.0)])
+def test_wide_fp64_samples_across_strips(dim, p):
+    """FP64 samples of 17 .. 32 components, whose strips run one to a workgroup
+    (four in general Lp): pairs over many strips and hand-over windows, tiles
+    composed from them, DTW, and a path whose blocks hold several strips."""
+    c = synth.random_pair(170 + dim, 171 + dim, 460, 520, dim, irregular=True, nu=0.02, lam=0.9, p=p)
+    A, TA, B, TB = host_inputs(c, "f64")
+    dA, dTA, dB, dTB = operands(c, "f64")
+    want = oracle.get().twed(A, TA, B, TB, c.nu, c.lam, c.p)
+    got = {}
+    for k in (0, 1, 2):
+        say(f"pair dim {dim} p {p} K={k}")
+        got[k] = float(tw.twed_pair(dA, dTA, dB, dTB, c.nu, c.lam, c.p, "f64", strip_k=k).item())
+    assert got[0] == got[1] == got[2] and abs(got[0] - want) <= 1e-12 * want
+    say(f"tiles dim {dim} p {p}")
+    for k in (0, 2):
+        assert _grid_sweep(dA, dTA, dB, dTB, c, "f64", [200, 331], [130, 389], strip_k=k) == got[0]
+    dtw = oracle.get().dtw(A.reshape(len(A), -1), B.reshape(len(B), -1), p)
+    for k in (0, 2):
+        say(f"dtw dim {dim} p {p} K={k}")
+        v = float(tw.twed_dp("dtw", dA, dB, p=p, precision="f64", strip_k=k).item())
+        assert abs(v - dtw) <= 1e-12 * dtw
+    say(f"path dim {dim} p {p}")
+    d, path = tw.twed_pair_path(dA, dTA, dB, dTB, c.nu, c.lam, c.p, "f64", block=256)
+    cost = oracle.get().path_cost(A, TA, B, TB, c.nu, c.lam, c.p, path.cpu().numpy())
+    assert float(d.item()) == got[0] and abs(cost - want) <= 1e-12 * want
