@@ -572,9 +572,9 @@ int64_t batch_items(const BatchPlan &P)
 // is what that kernel holds, not where it stops being the faster one: it sweeps
 // 64 pairs a workgroup, so few or long series leave it with little to run side by
 // side.  Against a wave per pair, FP64 and FP32, 1 .. 28 components and 1 .. 32
-// rows: 60,000 series of 20 .. 36 samples 1.2 .. 11 times as fast, 2,000 series of
-// 28 samples 0.9 .. 4 times, 60 series 0.3 .. 0.7 times, 500 series of 400 .. 600
-// samples 0.06 .. 0.2 times (twed_batch_plan_tune measures both and keeps the
+// rows: 60,000 series of 20 .. 36 samples 2.2 .. 12 times as fast, 2,000 series of
+// 28 samples 1.1 .. 2.8 times, 60 series 0.33 .. 0.69 times, 500 series of
+// 400 .. 600 samples 0.07 .. 0.19 times (twed_batch_plan_tune measures both and keeps the
 // faster).
 bool lane_eligible(const BatchPlan &P) { return !P.sym && !P.list && P.nX == 1 && P.maxX <= kLaneMaxQuery; }
 
