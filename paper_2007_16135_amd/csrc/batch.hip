@@ -231,6 +231,29 @@ __device__ __forceinline__ int64_t lane_value64(int64_t v, int lane)
                      (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(uint64_t)v, lane));
 }
 
+// Whether the chain's steps are held apart so that each row read stays a whole
+// step ahead of its use.  1-D samples: left to itself the compiler reads the rows
+// of two steps at the end of the first, and the wave waits out the LDS latency
+// once in two steps (all pairs of 400 series: FP64 of 57 samples 320 us, now 260;
+// FP32 of 569 4.57 ms, now 4.03, of 1,017 12.2, now 11.4).  Not in FP64 above six
+// columns, where kStepsAligned does it for less, nor at 10 and 11 FP32 columns,
+// which lose 2 .. 6% (of 633 4.73 ms without, 5.00 with) though their loops are
+// the others' instructions in the others' order.  Wider samples lose (20,000 pairs
+// of 310 4-D FP32 samples 955 us without, 1,049 with).
+template <typename CT, typename AT, int DIMT, int K>
+constexpr bool kReadsPinned = DIMT == 1 && (sizeof(CT) == 8   ? K <= 6
+                                            : sizeof(AT) == 4 ? K != 10 && K != 11
+                                                              : true);
+
+// Whether a step begins at an even word of the code.  FP64 steps are runs of
+// 8-byte instructions, and one that begins at an odd word takes 15 .. 19% longer:
+// where a loop falls is the accident of the code before it (all pairs of 400 1-D
+// series, ms, odd and even: of 761 samples 16.3 and 13.6, of 1,017 28.0 and 22.8;
+// of 633 11.9 and 9.7).  The operands put the directive before the step's first
+// instruction and the next row's read behind it, a step ahead.
+template <typename CT, int DIMT, int K>
+constexpr bool kStepsAligned = DIMT == 1 && sizeof(CT) == 8 && K > 6;
+
 // Sweeps the chain described by sh.start and sh.base (E series of `rows`)
 // against the nB columns of rowsB.  Lane e gets DP(nA_e, nB) of series e.
 template <typename CT, typename AT, int DIMT, int PM, int K>
@@ -338,16 +361,12 @@ __device__ __forceinline__ AT sweep_chain(ChainShared<CT, DIMT> &sh, const CT *_
             const int ev = t_in < t_out ? t_in : t_out;
             const int lim = ev < stop ? ev + 1 : stop;
             // two steps per iteration: the band registers alternate without copies
-            // 1-D samples: the barriers keep each row read a whole step ahead of its
-            // use.  Left to itself the compiler moves it next to its use, and a wave
-            // alone on its SIMD waits out the LDS latency in every second step (780
-            // pairs of 400 FP64 samples 104 us, now 96; of 1,000 391, now 351).
-            // Wider samples lose more by keeping the steps apart (20,000 pairs of 310
-            // 4-D FP32 samples 955 us without, 1,049 with).
             auto ahead = [] {
-                if constexpr (DIMT == 1) __builtin_amdgcn_sched_barrier(0);
+                if constexpr (kReadsPinned<CT, AT, DIMT, K>) __builtin_amdgcn_sched_barrier(0);
             };
             for (; t + 2 <= lim; t += 2) {
+                if constexpr (kStepsAligned<CT, DIMT, K>)
+                    asm volatile(".p2align 3" : "+v"(ra.x[0]), "+v"(ra.t), "+v"(ra.del));
                 load_row<CT, DIMT>(pr, 1, rb);
                 ahead();
                 step(ra);
